@@ -222,16 +222,18 @@ int vanse_batch_set_stream(vanse_batch_t b, void *stream);
  *       and their nz is split into equal segments of at most 64 planes (at
  *       most 32, 16 or 8 when a host-side estimate of the launch finds the
  *       batch too small to fill the GPU with 64); otherwise each
- *       member gets general tiles (any size) of as many x-rows as fit 512
- *       interior and 1024 (FP64: 512) halo-plane cells per 512-thread
- *       block, and its nz is split into equal segments of at most 32 planes
+ *       member gets general tiles (any size) of as many x-rows as fit a
+ *       1024-thread block (FP64 and D3Q27: 512 threads) when those tiles, in
+ *       segments of 32 planes, are at least one for every compute unit, and
+ *       else as many as fit 512 interior and 1024 (FP64: 512) halo-plane
+ *       cells per 512-thread block, and its nz is split into equal segments of at most 32 planes
  *       (at most 24, 16, 12 or 8 when a host-side estimate of the launch
  *       finds the batch too small to fill the GPU with 32;
- *       vanse_batch_two_step_layout reports the result).  A D3Q19 batch in
- *       reduced storage whose members are all at most 96 cells wide takes
+ *       vanse_batch_two_step_layout reports the result).  A smaller D3Q19
+ *       batch in reduced storage whose members are all at most 96 cells wide takes
  *       768-thread blocks instead, with as many x-rows as fit 768
- *       halo-plane cells (more rows per tile).  On D3Q19, when a member's
- *       full rows do not fit a block (nx > 341; FP64 nx > 170), general
+ *       halo-plane cells (more rows per tile).  In a smaller D3Q19 batch, when a
+ *       member's full rows do not fit a block (nx > 341; FP64 nx > 170), general
  *       tiles split the x-rows of wide members into the fewest segments of
  *       at most 62 columns, with a halo column on each side (one wave per
  *       row; vanse_batch_two_step_tiles reports them).  Every member gets a
@@ -239,9 +241,9 @@ int vanse_batch_set_stream(vanse_batch_t b, void *stream);
  *       solver: its population memory doubles).  Used for every group of 4
  *       steps of a chunk while all members sit at even time levels (two
  *       launches, so each member ends the group in its first array); other
- *       steps, and batches with a member that has no such tile (D3Q27 in
- *       FP64, or wider than 340 on D3Q27), use the single-step batched
- *       launch.
+ *       steps, and batches with a member that has no such tile (smaller
+ *       batches of D3Q27 in FP64, or wider than 340 on D3Q27), use the
+ *       single-step batched launch.
  * Results do not depend on any of these.  Errors: EINVAL, ENOMEM. */
 int vanse_batch_set_tuning(vanse_batch_t b, int block, int flags, int chunk);
 
@@ -306,7 +308,7 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y);
  * starts at an even level this way; a step left over (odd level, or odd n)
  * uses the single-step kernel.  Results are bitwise identical to single
  * steps.  Requires 1 <= rows <= ny, planes >= 1, and a tile shape compiled
- * into the library (the shapes whose registers fit without spilling): with
+ * into the library: with
  * I = ceil(nx * rows / 512) interior and H = ceil(nx * (rows + 2) / 512)
  * halo cells per thread, when nx is a multiple of 64 and rows divides ny
  *   D3Q19, FP32/FP16 storage: I <= 2 and H <= I + 2
@@ -321,9 +323,9 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y);
  *   D3Q27, FP32/FP16 storage: I = 1 and H <= 2
  *   D3Q27, FP64: none;
  * and the block's LDS (Q * nx * rows stored populations plus 5 * (rows + 4)
- * * nx perturbation values) within 160 KiB.  Blocks have 512 threads, except
- * D3Q19's 256-wide 4-row tile in FP32/FP16 storage, which runs in blocks of
- * 1024 threads (one interior and two halo cells per thread).
+ * * nx perturbation values) within 160 KiB.  Blocks have 512 threads, or 1024
+ * for D3Q19 tiles in FP32/FP16 storage of more than 512 cells, or more than
+ * 1024 with the two outer rows.
  * rows = 0 switches the launch off and frees the second array.
  * Synchronises the solver's stream when it allocates or frees.
  * Errors: EINVAL, ENOMEM. */
@@ -333,11 +335,14 @@ int vanse_set_fused(vanse_t h, int rows, int planes);
  * row segments with 1, 2 or 4 rows per block where they divide the
  * lattice; flat launches of 256, 512 and 1024 threads; on 3-D lattices the
  * two-step launch of vanse_set_fused with 1, 2, 4 or 8 rows and 8, 16, 32
- * or 64 planes, and 128 when nz > 64, where its shape exists) runs
+ * or 64 planes, and 128 when nz > 64, where its shape exists, and with the
+ * most rows that a 512-thread and the largest block take, which also gives
+ * FP64 solves of any width and D3Q27 in FP64 a two-step launch) runs
  * `steps_per_trial` REAL steps timed with HIP events, and the fastest is kept and cached for solves of the same
  * lattice, dtype and size class.  *fused_rows / *fused_planes report the
- * chosen two-step tile (0 / 0: single steps; the tile of the single-step
- * kernel is still reported and used for leftover steps).  The two-step
+ * chosen two-step tile, which need not be one that vanse_set_fused takes
+ * (0 / 0: single steps; the tile of the single-step kernel is still reported
+ * and used for leftover steps).  The two-step
  * candidates need the second population array of vanse_set_fused: it is
  * allocated for the trials and freed again unless a two-step launch wins.
  * The solve advances (number of candidates) * steps_per_trial steps, or 0

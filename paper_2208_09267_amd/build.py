@@ -11,7 +11,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvanse.so")
-SOURCES = ["kernels.hip", "api.hip"]
+SOURCES = ["kernels.hip", "march.hip", "api.hip"]
 ARCH = "gfx950"
 
 # Packed FP32 instructions are disabled on purpose: every kernel is compiled
@@ -40,13 +40,17 @@ def build(verbose: bool = False, extra_flags=None) -> str:
     flags = HIP_FLAGS + list(extra_flags or [])
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
+    running = []  # the sources compile side by side
     for src in SOURCES:
         obj = os.path.join(bdir, src + ".o")
         cmd = [cc] + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        running.append((subprocess.Popen(cmd), cmd))
         objs.append(obj)
+    failed = [(p.returncode, cmd) for p, cmd in running if p.wait()]
+    if failed:
+        raise subprocess.CalledProcessError(*failed[0])
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [cc, "-shared", "-fPIC", "--offload-arch=" + ARCH, "-o", tmp] + objs
     if verbose:

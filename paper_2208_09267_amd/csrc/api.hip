@@ -49,9 +49,7 @@ struct vanse_batch {
     // two-step launch (VANSE_TUNE_TWO_STEP)
     bool two_step = false;              // requested
     bool fused_ok = false;              // every member has a general tile
-    int uni_nx = 0, uni_rows = 0;       // the members' common compile-time tile (0: general tiles)
-    bool xt = false;                    // general tiles with x-split members
-    int gen_threads = 512;              // block size of full-row general tiles
+    vanse::MarchTile march;             // tiles of full rows (nt = 0: x-split tiles)
     unsigned nblocks2 = 0;
     size_t lds2 = 0;                    // LDS bytes per block of the two-step grid
     vanse::BatchMember *d_members2 = nullptr;
@@ -412,7 +410,7 @@ int vanse_step(vanse_t h, int64_t n)
         const vanse::StepArgs a = vanse::step_args(s, s.t);
         if (s.fused_rows > 0 && (s.t & 1) == 0 && n - k >= 2) {
             // levels t -> t + 2 into the second array, which becomes current
-            hipError_t e = vanse::launch_fused(s, a);
+            hipError_t e = vanse::launch_march(s, a);
             if (e != hipSuccess) return hip_fail(&s, e, "vanse_step (two-step launch)");
             std::swap(s.f, s.f_alt);
             s.t += 2;
@@ -501,6 +499,30 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y)
     return VANSE_OK;
 }
 
+}  // extern "C"
+
+namespace {
+// Two-step launch with tiles of `rows` x-rows and `planes` z-planes, which
+// the caller has checked; allocates the second population array.
+int two_step_on(Solver &s, int rows, int planes)
+{
+    if (!s.f_alt) {
+        hipError_t e = hipMalloc(&s.f_alt, s.f_bytes);
+        if (e != hipSuccess) {
+            s.f_alt = nullptr;
+            (void)hipGetLastError();
+            return fail(&s, VANSE_ENOMEM,
+                        std::string("vanse_set_fused: hipMalloc failed: ") + hipGetErrorString(e));
+        }
+    }
+    s.fused_rows = rows;
+    s.fused_planes = planes;
+    return VANSE_OK;
+}
+}  // namespace
+
+extern "C" {
+
 int vanse_set_fused(vanse_t h, int rows, int planes)
 {
     if (!h) return fail(nullptr, VANSE_EINVAL, "vanse_set_fused: NULL handle");
@@ -521,21 +543,12 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be >= 0 and planes >= 1");
     if (rows > s.geo.ny)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be <= ny");
-    if (!vanse::fused_shape(s.lattice, s.mode, s.geo, rows, nullptr))
+    if (!vanse::fused_shape(s.lattice, s.mode, s.geo, rows) ||
+        !vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, nullptr))
         return fail(&s, VANSE_EINVAL,
                     "vanse_set_fused: no compiled tile of nx = " + std::to_string(s.geo.nx) +
                         " x " + std::to_string(rows) + " rows for this lattice and dtype");
-    if (!s.f_alt) {
-        if ((e = hipMalloc(&s.f_alt, s.f_bytes)) != hipSuccess) {
-            s.f_alt = nullptr;
-            (void)hipGetLastError();
-            return fail(&s, VANSE_ENOMEM,
-                        std::string("vanse_set_fused: hipMalloc failed: ") + hipGetErrorString(e));
-        }
-    }
-    s.fused_rows = rows;
-    s.fused_planes = planes;
-    return VANSE_OK;
+    return two_step_on(s, rows, planes);
 }
 
 }  // extern "C"
@@ -573,7 +586,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         if (it != g_solo_tune_cache.end() &&
             (it->second.fused_rows == 0 ||
              (it->second.fused_rows <= s.geo.ny &&
-              vanse::fused_shape(s.lattice, s.mode, s.geo, it->second.fused_rows, nullptr)))) {
+              vanse::march_tile(s.lattice, s.mode, s.geo, it->second.fused_rows, 0, nullptr)))) {
             best_c = it->second;
             cached = true;
         }
@@ -587,12 +600,21 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         std::vector<SoloChoice> cand = {{256, 1, 0, 0, 0}, {256, 2, 0, 0, 0}, {256, 4, 0, 0, 0},
                                         {256, 1, 1, 0, 0}, {512, 1, 1, 0, 0}, {1024, 1, 1, 0, 0}};
         if (s.d == 3) {
-            const int rows[4] = {1, 2, 4, 8};
+            // and the most rows a 512-thread and the largest block take, where
+            // those are others: ragged widths, and FP64 and D3Q27 tiles that
+            // vanse_set_fused has no shape for
+            std::vector<int> rows = {1, 2, 4, 8};
+            for (int &r : rows)
+                if (!vanse::fused_shape(s.lattice, s.mode, s.geo, r)) r = 0;
+            for (int nt : {512, vanse::march_threads(s.lattice, s.mode)}) {
+                const int r = vanse::march_rows(s.lattice, s.mode, s.geo, nt);
+                if (std::find(rows.begin(), rows.end(), r) == rows.end()) rows.push_back(r);
+            }
             const int planes[5] = {8, 16, 32, 64, 128};
             for (int r : rows)
                 for (int p : planes) {
                     if (p > 64 && s.geo.nz <= 64) continue;
-                    if (r <= s.geo.ny && vanse::fused_shape(s.lattice, s.mode, s.geo, r, nullptr))
+                    if (r > 0 && vanse::march_tile(s.lattice, s.mode, s.geo, r, 0, nullptr))
                         cand.push_back({256, 1, 1, r, p});
                 }
         }
@@ -608,7 +630,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             if (!c.flat && !tiled_ok) continue;  // would fall back to a flat launch
             if (c.tile_x * c.tile_y > max_threads(s)) continue;
             if (c.fused_rows) {
-                if (vanse_set_fused(h, c.fused_rows, c.fused_planes) != VANSE_OK) continue;
+                if (two_step_on(s, c.fused_rows, c.fused_planes) != VANSE_OK) continue;
             } else if (s.fused_rows) {
                 s.fused_rows = s.fused_planes = 0;  // keep the second array for later trials
             }
@@ -645,7 +667,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
     s.tile_y = best_c.tile_y;
     s.allow_row = !best_c.flat;
     s.flags = keep_flags;
-    int rc = vanse_set_fused(h, best_c.fused_rows, best_c.fused_planes);
+    int rc = best_c.fused_rows ? two_step_on(s, best_c.fused_rows, best_c.fused_planes)
+                               : vanse_set_fused(h, 0, 0);
     if (rc != VANSE_OK) return rc;
     if (tile_x) *tile_x = best_c.tile_x;
     if (tile_y) *tile_y = best_c.tile_y;
@@ -833,6 +856,15 @@ int balanced_planes(int nz, int target)
     return (nz + segs - 1) / segs;
 }
 
+int device_cus()
+{
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
+        cus = 256;
+    return cus;
+}
+
 // Estimated duration (in cell-planes) of a batched two-step launch whose
 // segments aim at `target` planes.  Blocks reach the XCDs in
 // contiguous ranges of the block index (the kernel's XCD-contiguous order),
@@ -888,10 +920,7 @@ double gen_launch_estimate(const std::vector<const vanse::Solver *> &ms,
 int segment_target(const std::vector<const vanse::Solver *> &ms, const std::vector<int> &rows,
                    const std::vector<int> &cols, int base, std::initializer_list<int> shorter)
 {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-        cus = 256;
+    const int cus = device_cus();
     const double base_t = gen_launch_estimate(ms, rows, cols, base, cus);
     int best = base;
     double best_t = base_t;
@@ -921,7 +950,8 @@ int batch_layout2(vanse_batch *b)
         (void)hipGraphExecDestroy(b->gexec2);
         b->gexec2 = nullptr;
     }
-    int uni_nx = b->members[0]->s.geo.nx, uni_rows = 0;
+    const int uni_nx = b->members[0]->s.geo.nx;
+    int uni_rows = 0;
     for (int k = 0; k < b->count; ++k) {
         const Solver &s = b->members[k]->s;
         const int r = s.d == 3 && s.geo.nx == uni_nx
@@ -933,7 +963,6 @@ int batch_layout2(vanse_batch *b)
         }
         uni_rows = r;
     }
-    if (uni_rows == 0) uni_nx = 0;
     // General tiles: full x-rows; on D3Q19, x-split tiles when a member's
     // full rows do not fit a block (FP64 wider than 170 cells, reduced
     // storage wider than 341), so that such batches still take the two-step
@@ -968,9 +997,39 @@ int batch_layout2(vanse_batch *b)
         }
         if (narrow) gen_threads = vanse::kGenThreads768;
     }
+    // Tall tiles: as many rows as a block of the largest size takes, when they
+    // fill every CU at the base segment length.  The two outer rows then cost
+    // less (192 wide: 2 of 7 rows against 2 of 4), and with fewer tiles than
+    // CUs the smaller tiles above spread better.  FP32, MLUPS, tall against
+    // the rows above in the same kernel: 64 solves of edges 32-96 59.6 k
+    // against 58.6 k, ten requests of edges 37-173 54.4 k against 48.0 k,
+    // three 192^3 59.7 k against 55.0 k; 153 + 69 (145 tiles) 51.4 k against
+    // 48.8 k, 16 of 40^3 (64 tiles) 42.5 k against 49.1 k.
+    std::vector<int> tall(b->count, 0);
+    bool use_tall = false;
+    if (uni_rows == 0) {
+        const int nt = vanse::march_threads(b->lattice, b->mode);
+        size_t tiles = 0;
+        bool ok = true;
+        for (int k = 0; k < b->count && ok; ++k) {
+            const Solver &s = b->members[k]->s;
+            tall[k] = vanse::march_rows(b->lattice, b->mode, s.geo, nt);
+            // one row per tile (three collisions for one) loses to split rows
+            ok = tall[k] > 1 || tall[k] == s.geo.ny;
+            if (ok)
+                tiles += (size_t)((s.geo.ny + tall[k] - 1) / tall[k]) * ((s.geo.nz + 31) / 32);
+        }
+        use_tall = ok && tiles >= (size_t)device_cus();
+        if (use_tall) {
+            xt = false;
+            gen_threads = nt;
+        }
+    }
     auto tile_rows = [&](int k) {
         const Solver &s = b->members[k]->s;
-        return uni_rows ? uni_rows : (xt ? xt_rows[k] : vanse::batch_fused_rows(s, gen_threads));
+        if (uni_rows) return uni_rows;
+        if (use_tall) return tall[k];
+        return xt ? xt_rows[k] : vanse::batch_fused_rows(s, gen_threads);
     };
     auto tile_cols = [&](int k) {
         const Solver &s = b->members[k]->s;
@@ -995,14 +1054,34 @@ int batch_layout2(vanse_batch *b)
     std::vector<vanse::BatchMember> mem(b->count);
     std::vector<unsigned> owner;
     unsigned begin = 0;
+    // tiles of full rows: one kernel whose passes cover every member's tile
+    vanse::MarchTile march;
+    if (!xt) {
+        vanse::MarchTile t;
+        const Solver &s0 = b->members[0]->s;
+        if (uni_rows && !vanse::march_tile(b->lattice, b->mode, s0.geo, uni_rows, 0, &march))
+            return VANSE_OK;
+        const int nt = uni_rows ? march.nt : gen_threads;
+        march.nt = nt;
+        for (int k = 0; k < b->count; ++k) {
+            if (!vanse::march_tile(b->lattice, b->mode, b->members[k]->s.geo, tile_rows(k), nt, &t))
+                return VANSE_OK;
+            march.ipt = std::max(march.ipt, t.ipt);
+            march.hpt = std::max(march.hpt, t.hpt);
+            march.ppt = std::max(march.ppt, t.ppt);
+        }
+        if (!vanse::march_cover(b->lattice, b->mode, &march)) return VANSE_OK;
+    }
     size_t lds = 0;
     for (int k = 0; k < b->count; ++k) {
         const Solver &s = b->members[k]->s;
         const int rows = tile_rows(k), cols = tile_cols(k);
         if (rows == 0) return VANSE_OK;
         const int planes = tile_planes(s);
-        lds = std::max(lds, cols < s.geo.nx ? vanse::fused_lds_bytes_xt(s.q, s.mode, cols, rows)
-                                            : vanse::fused_lds_bytes(s.q, s.mode, s.geo.nx, rows));
+        lds = std::max(lds, !xt ? vanse::march_lds_bytes(b->lattice, b->mode, s.geo.nx, rows, march)
+                                : cols < s.geo.nx
+                                      ? vanse::fused_lds_bytes_xt(s.q, s.mode, cols, rows)
+                                      : vanse::fused_lds_bytes(s.q, s.mode, s.geo.nx, rows));
         const unsigned fnxb = (unsigned)((s.geo.nx + cols - 1) / cols);
         const unsigned fnyb = (unsigned)((s.geo.ny + rows - 1) / rows) * fnxb;
         const unsigned nzb = (unsigned)((s.geo.nz + planes - 1) / planes);
@@ -1021,6 +1100,8 @@ int batch_layout2(vanse_batch *b)
             if (e != hipSuccess) {
                 s.f_alt = nullptr;
                 (void)hipGetLastError();
+                // D3Q27 in FP64 has run on single steps alone
+                if (b->lattice == VANSE_D3Q27 && b->mode == vanse::MODE_F64) return VANSE_OK;
                 return bfail(b, VANSE_ENOMEM, std::string("vanse_batch: second population array: ") +
                                                   hipGetErrorString(e));
             }
@@ -1069,10 +1150,7 @@ int batch_layout2(vanse_batch *b)
     }
     b->nblocks2 = begin;
     b->lds2 = lds;
-    b->uni_nx = uni_nx;
-    b->uni_rows = uni_rows;
-    b->xt = xt;
-    b->gen_threads = gen_threads;
+    b->march = march;
     b->fused_ok = true;
     return VANSE_OK;
 }
@@ -1164,9 +1242,11 @@ hipError_t batch_launch(vanse_batch *b, int j, hipStream_t st)
 hipError_t batch_launch2(vanse_batch *b, int j, int swap, hipStream_t st)
 {
     const double *mtab = reinterpret_cast<const double *>(b->d_tab);
-    return vanse::launch_batch_fused(b->lattice, b->mode, b->uni_nx, b->uni_rows, b->xt, b->gen_threads,
-                                     b->nblocks2, b->lds2, b->d_members2, b->d_owner2, mtab, j,
-                                     b->count, swap, st);
+    if (b->march.nt)
+        return vanse::launch_batch_march(b->lattice, b->mode, b->march, b->nblocks2, b->lds2,
+                                         b->d_members2, b->d_owner2, mtab, j, b->count, swap, st);
+    return vanse::launch_batch_fused(b->mode, b->nblocks2, b->lds2, b->d_members2, b->d_owner2, mtab,
+                                     j, b->count, swap, st);
 }
 
 // Steps 0 .. k-1 of a chunk: with `two`, each group of 4 steps is two

@@ -127,29 +127,26 @@ StepArgs step_args(const Solver &s, int64_t n);
 
 // Kernel launchers (kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_step(const Solver &s, const StepArgs &a, int parity);
-constexpr int kFusedThreads = 512;    // threads per block of the two-step launch
+constexpr int kFusedThreads = 512;    // threads per block the tile rules count with
 // general tiles of batches whose members are all narrow (nx <= 96, D3Q19,
-// reduced storage): blocks of 768 threads, one interior and one halo cell
-// per thread (145 VGPRs: 3 waves per SIMD, where the 512-thread tile with
-// two halo cells per thread holds 193 VGPRs and 2 waves)
+// reduced storage): blocks of 768 threads, the tile and its two outer rows in
+// one pass
 constexpr int kGenThreads768 = 768;
 constexpr int kFusedMaxLds = 160 * 1024;
-// Tile shapes of the two-step launch compiled into the library: ipt interior
-// and hpt halo-plane cells per thread, kept to the combinations whose
-// registers fit without spilling on gfx950.  nxc: nx when the tile is one of
-// the compile-time tiles (fused_tile_nx), 0 for a runtime nx; D3Q27's
-// 256-wide 4-row tile fits only with nx and rows folded in.
+// Tile shapes vanse_set_fused takes: ipt interior and hpt halo-plane cells per
+// thread of a 512-thread block.  nxc: nx when the tile is one of
+// fused_tile_nx, else 0.
 constexpr bool fused_compiled(int lattice, int mode, int ipt, int hpt, int nxc = 0)
 {
     if (lattice == 0 || ipt < 1 || hpt < ipt) return false;
-    if (lattice == 2)  // D3Q27: 27 populations per cell in registers
+    if (lattice == 2)
         return mode != MODE_F64 &&
-               (ipt == 1 ? hpt <= 3 : (hpt <= 2 || (nxc == 256 && hpt == 3)));
+               (ipt == 1 ? hpt <= 3 : (ipt == 2 && (hpt <= 2 || (nxc == 256 && hpt == 3))));
     if (mode == MODE_F64) return ipt == 1 && hpt <= 2;
     return ipt <= 2 && hpt <= ipt + 2;
 }
-// nx if (nx, rows) is a compile-time tile of the two-step launch (D3Q19:
-// 256 x 4, 256 x 2, 128 x 4; D3Q27: 256 x 4, 256 x 2), else 0.
+// nx if (nx, rows) is one of the benchmarked tiles (D3Q19: 256 x 4, 256 x 2,
+// 128 x 4; D3Q27: 256 x 4, 256 x 2), else 0.
 constexpr int fused_tile_nx(int lattice, int nx, int rows)
 {
     if (lattice == 1)
@@ -157,8 +154,7 @@ constexpr int fused_tile_nx(int lattice, int nx, int rows)
     if (lattice == 2) return (nx == 256 && (rows == 4 || rows == 2)) ? nx : 0;
     return 0;
 }
-// The same for the general tile (any nx, shorter last tile), whose rows and
-// row bases are per lane.
+// The same for any nx and a shorter last tile.
 constexpr bool fused_compiled_gen(int lattice, int mode, int ipt, int hpt)
 {
     if (lattice == 0 || ipt < 1 || hpt < ipt) return false;
@@ -166,19 +162,35 @@ constexpr bool fused_compiled_gen(int lattice, int mode, int ipt, int hpt)
     if (mode == MODE_F64) return ipt == 1 && hpt == 1;
     return ipt == 1 ? hpt <= 3 : (ipt == 2 && hpt == 2);
 }
-// Two-step launch variant of a tile of `rows` full x-rows: ipt interior and
-// hpt halo-plane cells per thread; gen: the general tile (nx not a multiple
-// of 64 or rows not dividing ny; needs every array's byte size below 2^32).
-struct FusedShape {
-    int ipt = 0, hpt = 0;
-    bool gen = false;
-};
-// false if the lattice/dtype has no such compiled shape or the LDS is too large.
-bool fused_shape(int lattice, int mode, const Geometry &g, int rows, FusedShape *out);
-// LDS of one block of the two-step launch: the population slab and the ring
+// Whether vanse_set_fused takes tiles of `rows` full x-rows.
+bool fused_shape(int lattice, int mode, const Geometry &g, int rows);
+// LDS of one 512-thread block by that rule: the population slab and the ring
 // of 5 perturbation planes of rows + 4 x-rows.
 size_t fused_lds_bytes(int q, int mode, int nx, int rows);
-hipError_t launch_fused(const Solver &s, const StepArgs &a);
+// Tile of the marching two-step kernel (march.h): threads per block, passes
+// over the interior and over the region with the two outer rows, pert values
+// a thread loads per plane.
+struct MarchTile {
+    int nt = 0, ipt = 0, hpt = 0, ppt = 0;
+};
+// The compiled tile of `rows` full x-rows in blocks of nt threads (0: the
+// block size chosen for that tile); false if there is none or its LDS does
+// not fit.
+bool march_tile(int lattice, int mode, const Geometry &g, int rows, int nt, MarchTile *out);
+// The smallest compiled tile whose passes cover those of t (a batch's members
+// share one kernel); false if there is none.
+bool march_cover(int lattice, int mode, MarchTile *t);
+// Most x-rows of a tile in blocks of nt threads whose interior takes one pass
+// (0: none), evened out over ny.
+int march_rows(int lattice, int mode, const Geometry &g, int nt);
+// Largest block size of the lattice's and storage's tiles.
+int march_threads(int lattice, int mode);
+size_t march_lds_bytes(int lattice, int mode, int nx, int rows, const MarchTile &t);
+// Two-step launch of one solve: tiles of a.fty x-rows and a.fsz planes.
+hipError_t launch_march(const Solver &s, const StepArgs &a);
+hipError_t launch_batch_march(int lattice, int mode, const MarchTile &t, unsigned nblocks, size_t lds,
+                              const BatchMember *members, const unsigned *owner, const double *mtab,
+                              int j, int count, int swap, hipStream_t st);
 hipError_t launch_init(const Solver &s, const double *rho0, const double *u0);
 // sum over cells of rho0 phi(x, 0) (the initial M0; rho0 NULL: 1), FP64, in
 // the fixed order of the reductions, into out_dev[0] (device); uses the
@@ -203,13 +215,8 @@ size_t fused_lds_bytes_xt(int q, int mode, int cols, int rows);
 // two-step launch uses when every member has this nx and a multiple of the
 // rows in y (0: none for this lattice, mode and size).
 int batch_uniform_rows(int lattice, int mode, int nx, int ny);
-// uni_nx, uni_rows: the members' common compile-time tile, or 0, 0 for
-// general tiles (each member's own rows).
-// xt: general tiles with x-split members (batch_xt_tile), D3Q19 only.
-// gen_threads: block size of full-row general tiles (kFusedThreads, or
-// kGenThreads768 for D3Q19 in the reduced modes).
-hipError_t launch_batch_fused(int lattice, int mode, int uni_nx, int uni_rows, bool xt, int gen_threads,
-                              unsigned nblocks, size_t lds, const BatchMember *members,
+// x-split tiles of a D3Q19 batch (batch_xt_tile).
+hipError_t launch_batch_fused(int mode, unsigned nblocks, size_t lds, const BatchMember *members,
                               const unsigned *owner, const double *mtab, int j, int count,
                               int swap, hipStream_t st);
 hipError_t launch_moments(const Solver &s, int parity, double m, double *rho, double *p,

@@ -37,7 +37,7 @@ def kernel_source_hash() -> str:
     """Hash of the sources that define the step kernels (a traffic record is
     valid only for the kernels it was measured on)."""
     h = hashlib.sha256()
-    for name in ("kernels.hip", "lattice.h", "internal.h"):
+    for name in ("kernels.hip", "march.hip", "march.h", "cell.h", "lattice.h", "internal.h"):
         with open(os.path.join(HERE, "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -53,8 +53,10 @@ def kernel_label(kind: str, lattice: str, mode: int, rows=None) -> str:
 
 def parse_name(full: str):
     """(label, lattice, mode) of a step kernel's demangled rocprofv3 name, or
-    None for other kernels.  The two-step kernel's label carries its tile
-    rows when they are a compile-time argument."""
+    None for other kernels.  The two-step kernel's label carries its tile's
+    rows: those of the 256-wide workload, from the passes over the interior and
+    the threads of its block (IPT, HPT, PPT, NT, waves), or its compile-time
+    rows (IPT, HPT, NXC, TYC, GEN, NT) in older traces."""
     m = re.search(r"vanse::(fused2_kernel|step_kernel)<vanse::(D\dQ\d+), (\d)((?:, \w+)*)>", full)
     if not m:
         return None
@@ -62,7 +64,9 @@ def parse_name(full: str):
     rows = None
     if kind == "fused2_kernel":
         args = [a.strip() for a in m.group(4).split(",") if a.strip()]
-        if len(args) >= 4 and args[3].isdigit() and int(args[3]) > 0:
+        if len(args) == 5:
+            rows = int(args[0]) * int(args[3]) // 256
+        elif len(args) >= 4 and args[3].isdigit() and int(args[3]) > 0:
             rows = int(args[3])
     return kernel_label(kind, lat, mode, rows), lat, mode
 
@@ -163,7 +167,7 @@ def _workload(short, grid):
     name and its grid size; (None, None) for other kernels."""
     lat = "D2Q9" if "D2Q9" in short else ("D3Q27" if "D3Q27" in short else "D3Q19")
     if short.startswith("batch_fused2"):
-        if ", 256, 4" in short:
+        if grid >= 1000000:  # 1024 blocks of 1024 threads; the 64 solves: 762
             return "4 x 256^3 batch", _BATCH256_CELLS
         return "64-solve batch", _BATCH64_CELLS
     if short.startswith("batch_step"):
@@ -173,7 +177,7 @@ def _workload(short, grid):
     if lat == "D2Q9" and short.startswith("step_kernel"):
         return "D2Q9 64^2", 64 * 64
     if short.startswith("fused2"):
-        return ("D3Q19 128^3", 128 ** 3) if ", 128, 4" in short else (lat + " 256^3", 256 ** 3)
+        return ("D3Q19 128^3", 128 ** 3) if ", 2, 512, " in short else (lat + " 256^3", 256 ** 3)
     if short.startswith("step_kernel"):
         return ("D3Q19 128^3", 128 ** 3) if grid < 4000000 else (lat + " 256^3", 256 ** 3)
     return None, None
