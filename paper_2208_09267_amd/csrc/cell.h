@@ -304,6 +304,19 @@ __device__ __forceinline__ R add_force(R F, R Fc, double fscale)
     else return F + Fc;
 }
 
+// a b + c rounded once to binary16, as a float.  The compiler makes this one
+// instruction of an FMA and the conversion that stores its result, but only
+// where both end up in one basic block; where a kernel's control flow parts
+// them the value was rounded to FP32 first, and about one in 2^13 differed
+// between kernels that must agree bitwise.  The rest population is the one
+// whose update ends in an FMA.
+__device__ __forceinline__ float fma_to_half(float a, float b, float c)
+{
+    unsigned h;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(a), "v"(b), "v"(c));
+    return __half2float(__ushort_as_half((unsigned short)h));
+}
+
 template <class L, int MODE, class R>
 __device__ __forceinline__ void collide(R (&v)[L::Q], R I, R gx, R gy, R gz, R omega,
                                         R fcoef, R Fex, R Fey, R Fez)
@@ -387,7 +400,9 @@ __device__ __forceinline__ void collide(R (&v)[L::Q], R I, R gx, R gy, R gz, R o
         constexpr R W0 = St::scaled ? R(1) : R(L::w[0]);
         constexpr R C0 = St::shifted ? R(-weight_excess<L, R>() / (St::scaled ? L::w[0] : 1.0))
                                      : R(0);
-        if constexpr (C0 != R(0))
+        if constexpr (MODE == MODE_F16S && C0 != R(0))
+            v[0] = fma_to_half(C0, P0, om1 * v[0] + W0 * P0);
+        else if constexpr (C0 != R(0))
             v[0] = om1 * v[0] + W0 * P0 + C0 * P0;
         else
             v[0] = om1 * v[0] + W0 * P0;

@@ -185,3 +185,13 @@ def test_batch_after_two_step_solo_steps_matches_single_steps():
     for m in mem:
         m.close()
 
+
+
+def test_fp16_two_step_equals_single_steps_at_large():
+    """One value in some 2^13 is where rounding to binary16 once or through
+    FP32 differs, which the small lattices above can miss."""
+    dims = (128, 128, 48)
+    (f1, *m1), (f2, *m2) = _pair("D3Q19", dims, vanse.FP16_SHIFTED, 4, 16, 0, 40, 3)
+    assert np.array_equal(f1, f2)
+    for a, b in zip(m1, m2):
+        assert np.array_equal(a, b)
