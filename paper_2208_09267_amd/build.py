@@ -11,7 +11,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvanse.so")
-SOURCES = ["kernels.hip", "march.hip", "api.hip"]
+SOURCES = ["kernels.hip", "march.hip", "box.hip", "api.hip"]
 ARCH = "gfx950"
 
 # Packed FP32 instructions are disabled on purpose: every kernel is compiled

@@ -408,6 +408,18 @@ int vanse_step(vanse_t h, int64_t n)
     int64_t k = 0;
     while (k < n) {
         const vanse::StepArgs a = vanse::step_args(s, s.t);
+        if (s.box > 0 && s.f_alt && (s.t & 1) == 0 && n - k >= 2) {
+            // levels t -> t + c (even) into the second array, which becomes current
+            const int c = (int)std::min<int64_t>(n - k, vanse::box_steps(s.lattice, s.box)) & ~1;
+            double m[vanse::kBoxMaxSteps];
+            for (int j = 0; j < c; ++j) m[j] = vanse::modulation(s.t + j, s.period);
+            hipError_t e = vanse::launch_box(s, a, s.box, m, c);
+            if (e != hipSuccess) return hip_fail(&s, e, "vanse_step (box launch)");
+            std::swap(s.f, s.f_alt);
+            s.t += c;
+            k += c;
+            continue;
+        }
         if (s.fused_rows > 0 && (s.t & 1) == 0 && n - k >= 2) {
             // levels t -> t + 2 into the second array, which becomes current
             hipError_t e = vanse::launch_march(s, a);
@@ -502,9 +514,10 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y)
 }  // extern "C"
 
 namespace {
-// Two-step launch with tiles of `rows` x-rows and `planes` z-planes, which
-// the caller has checked; allocates the second population array.
-int two_step_on(Solver &s, int rows, int planes)
+// Launches of several steps: tiles of `rows` x-rows and `planes` z-planes, or
+// the D2Q9 box kind `box`, which the caller has checked; allocates the second
+// population array.
+int multi_step_on(Solver &s, int rows, int planes, int box)
 {
     if (!s.f_alt) {
         hipError_t e = hipMalloc(&s.f_alt, s.f_bytes);
@@ -517,6 +530,7 @@ int two_step_on(Solver &s, int rows, int planes)
     }
     s.fused_rows = rows;
     s.fused_planes = planes;
+    s.box = box;
     return VANSE_OK;
 }
 }  // namespace
@@ -535,7 +549,7 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
             (void)hipFree(s.f_alt);
             s.f_alt = nullptr;
         }
-        s.fused_rows = s.fused_planes = 0;
+        s.fused_rows = s.fused_planes = s.box = 0;
         return VANSE_OK;
     }
     if (s.d != 3) return fail(&s, VANSE_EINVAL, "vanse_set_fused: 3-D lattices only");
@@ -548,14 +562,14 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
         return fail(&s, VANSE_EINVAL,
                     "vanse_set_fused: no compiled tile of nx = " + std::to_string(s.geo.nx) +
                         " x " + std::to_string(rows) + " rows for this lattice and dtype");
-    return two_step_on(s, rows, planes);
+    return multi_step_on(s, rows, planes, 0);
 }
 
 }  // extern "C"
 
 namespace {
 struct SoloChoice {
-    int tile_x, tile_y, flat, fused_rows, fused_planes;
+    int tile_x, tile_y, flat, fused_rows, fused_planes, box;
 };
 std::mutex g_solo_tune_mu;
 // (lattice, mode, log2 cells, nx, ny % 8) -> launch shape
@@ -574,7 +588,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
     int cls = 0;
     while ((int64_t(1) << (cls + 1)) <= (int64_t)s.geo.ncells) ++cls;
     const auto key = std::make_tuple(s.lattice, s.mode, cls, s.geo.nx, s.geo.ny % 8);
-    SoloChoice best_c{256, 1, 0, 0, 0};
+    SoloChoice best_c{256, 1, 0, 0, 0, 0};
     int64_t run = 0;
     bool cached = false;
     {
@@ -597,8 +611,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         // rows, and the flattened launch with 256, 512, 1024 threads; then the
         // two-step launch with 1, 2, 4, 8 rows and 8, 16, 32, 64 planes (and
         // 128 when the lattice has more than 64 planes)
-        std::vector<SoloChoice> cand = {{256, 1, 0, 0, 0}, {256, 2, 0, 0, 0}, {256, 4, 0, 0, 0},
-                                        {256, 1, 1, 0, 0}, {512, 1, 1, 0, 0}, {1024, 1, 1, 0, 0}};
+        std::vector<SoloChoice> cand = {{256, 1, 0, 0, 0, 0}, {256, 2, 0, 0, 0, 0}, {256, 4, 0, 0, 0, 0},
+                                        {256, 1, 1, 0, 0, 0}, {512, 1, 1, 0, 0, 0}, {1024, 1, 1, 0, 0, 0}};
         if (s.d == 3) {
             // and the most rows a 512-thread and the largest block take, where
             // those are others: ragged widths, and FP64 and D3Q27 tiles that
@@ -615,9 +629,14 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
                 for (int p : planes) {
                     if (p > 64 && s.geo.nz <= 64) continue;
                     if (r > 0 && vanse::march_tile(s.lattice, s.mode, s.geo, r, 0, nullptr))
-                        cand.push_back({256, 1, 1, r, p});
+                        cand.push_back({256, 1, 1, r, p, 0});
                 }
         }
+        // D2Q9: boxes of several steps, each twice (the faster run counts: a
+        // trial of a few launches lasts tens of microseconds)
+        if (steps_per_trial >= 2)
+            for (int kind = 1; vanse::box_steps(s.lattice, kind) > 0; ++kind)
+                for (int run2 = 0; run2 < 2; ++run2) cand.push_back({256, 1, 1, 0, 0, kind});
         hipEvent_t e0, e1;
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
             return fail(&s, VANSE_EDEVICE, "vanse_autotune: event creation failed");
@@ -629,10 +648,10 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             const bool tiled_ok = s.geo.nx % c.tile_x == 0 && s.geo.ny % c.tile_y == 0;
             if (!c.flat && !tiled_ok) continue;  // would fall back to a flat launch
             if (c.tile_x * c.tile_y > max_threads(s)) continue;
-            if (c.fused_rows) {
-                if (two_step_on(s, c.fused_rows, c.fused_planes) != VANSE_OK) continue;
-            } else if (s.fused_rows) {
-                s.fused_rows = s.fused_planes = 0;  // keep the second array for later trials
+            if (c.fused_rows || c.box) {
+                if (multi_step_on(s, c.fused_rows, c.fused_planes, c.box) != VANSE_OK) continue;
+            } else {
+                s.fused_rows = s.fused_planes = s.box = 0;  // keep the second array for later trials
             }
             s.tile_x = c.tile_x;
             s.tile_y = c.tile_y;
@@ -648,7 +667,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
                 best = ms;
                 best_c = c;
             }
-            if (rc == VANSE_OK && !c.fused_rows && ms < best_single) {
+            if (rc == VANSE_OK && !c.fused_rows && !c.box && ms < best_single) {
                 best_single = ms;
                 single_c = c;
             }
@@ -667,8 +686,9 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
     s.tile_y = best_c.tile_y;
     s.allow_row = !best_c.flat;
     s.flags = keep_flags;
-    int rc = best_c.fused_rows ? two_step_on(s, best_c.fused_rows, best_c.fused_planes)
-                               : vanse_set_fused(h, 0, 0);
+    int rc = best_c.fused_rows || best_c.box
+                 ? multi_step_on(s, best_c.fused_rows, best_c.fused_planes, best_c.box)
+                 : vanse_set_fused(h, 0, 0);
     if (rc != VANSE_OK) return rc;
     if (tile_x) *tile_x = best_c.tile_x;
     if (tile_y) *tile_y = best_c.tile_y;

@@ -104,7 +104,8 @@ struct Solver {
     size_t f_bytes = 0;
     int fused_rows = 0;          // two-step launch: x-rows per tile (0 = off)
     int fused_planes = 0;        //   and z-planes per segment
-    void *f_alt = nullptr;       // second population array of the two-step launch
+    int box = 0;                 // D2Q9: box kind of launches of several steps (0 = off)
+    void *f_alt = nullptr;       // second population array of these launches
     void *pert = nullptr;        // phi perturbation (double or float)
     size_t pert_bytes = 0;
     void *force = nullptr;       // per-cell force density (double or float), optional
@@ -191,6 +192,19 @@ hipError_t launch_march(const Solver &s, const StepArgs &a);
 hipError_t launch_batch_march(int lattice, int mode, const MarchTile &t, unsigned nblocks, size_t lds,
                               const BatchMember *members, const unsigned *owner, const double *mtab,
                               int j, int count, int swap, hipStream_t st);
+// Several steps of D2Q9 on boxes of cells in LDS (box.hip).
+constexpr int kBoxMaxSteps = 8;
+struct BoxSteps {
+    int k;                     // steps of this launch (even)
+    unsigned nbx;              // boxes per row of boxes
+    FastDiv fd_x;
+    double m[kBoxMaxSteps];    // modulations m(n) .. m(n + k - 1)
+};
+// Most steps of a launch of box `kind` (1, 2, ..); 0: no such box.
+int box_steps(int lattice, int kind);
+// k steps (even, at most box_steps) from a.f at an even level into a.f2; m: the
+// modulation of each.
+hipError_t launch_box(const Solver &s, const StepArgs &a, int kind, const double *m, int k);
 hipError_t launch_init(const Solver &s, const double *rho0, const double *u0);
 // sum over cells of rho0 phi(x, 0) (the initial M0; rho0 NULL: 1), FP64, in
 // the fixed order of the reductions, into out_dev[0] (device); uses the
