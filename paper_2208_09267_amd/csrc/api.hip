@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -153,28 +154,74 @@ size_t elem_bytes(int mode)
     return mode == vanse::MODE_F64 ? 8 : (mode == vanse::MODE_F32S ? 4 : 2);
 }
 
+// Pinned slots for results the host waits for (HostSlot), shared by all
+// solvers: a call takes one and gives it back before it returns, so there are
+// as many as calls have ever run at once, 32 to a page that is kept until the
+// process ends.
+std::mutex g_slot_mu;
+std::vector<vanse::HostResult> g_slots;
+std::atomic<unsigned long long> g_tickets{0};  // one count for every kind of call
+
+// Run `launch`, which writes its results to the slot it is given and raises its
+// flag last, and wait for that; the results go to out[0 .. n-1].
+template <class Fn>
+hipError_t host_result(hipStream_t st, double *out, int n, Fn &&launch)
+{
+    vanse::HostResult r;
+    {
+        std::lock_guard<std::mutex> lk(g_slot_mu);
+        if (g_slots.empty()) {
+            constexpr int count = 4096 / sizeof(vanse::HostSlot);
+            vanse::HostSlot *page = nullptr, *dev = nullptr;
+            hipError_t e = hipHostMalloc((void **)&page, 4096,
+                                         hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
+            if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&dev, page, 0);
+            if (e != hipSuccess) return e;
+            std::memset(page, 0, 4096);
+            for (int k = 0; k < count; ++k) {
+                vanse::HostResult q;
+                q.slot = page + k;
+                q.dev = dev + k;
+                g_slots.push_back(q);
+            }
+        }
+        r = g_slots.back();
+        g_slots.pop_back();
+    }
+    r.ticket = ++g_tickets;
+    hipError_t e = launch(r);
+    if (e == hipSuccess) {
+        // poll for up to a millisecond (the answer of an idle stream is here in
+        // microseconds), then wait for the stream, which also reports its errors
+        const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+        auto done = [&] { return __atomic_load_n(&r.slot->flag, __ATOMIC_ACQUIRE) == r.ticket; };
+        while (!done() && std::chrono::steady_clock::now() < until) __builtin_ia32_pause();
+        if (!done()) {
+            e = hipStreamSynchronize(st);
+            if (e == hipSuccess && !done()) e = hipErrorUnknown;
+        }
+    }
+    if (e != hipSuccess) return e;  // the slot may still be written: not given back
+    std::memcpy(out, r.slot->v, sizeof(double) * (size_t)n);
+    std::lock_guard<std::mutex> lk(g_slot_mu);
+    g_slots.push_back(r);
+    return hipSuccess;
+}
+
 // min, max and number of non-finite values of n caller-provided FP64 values
-// (device), through the solver's reduction scratch; synchronises its stream.
+// (device), through the solver's reduction scratch; waits for the answer.
 hipError_t check_range(Solver &s, const double *src, long long n, double *lo, double *hi,
                        double *bad)
 {
-    static thread_local double host[3 * vanse::kReduceBlocks];
-    hipError_t e = vanse::launch_range(src, n, s.scratch, s.stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(host, s.scratch, sizeof(double) * 3 * vanse::kReduceBlocks,
-                           hipMemcpyDeviceToHost, s.stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s.stream);
+    double v[3];
+    hipError_t e = host_result(s.stream, v, 3, [&](const vanse::HostResult &r) {
+        return vanse::launch_range(src, n, s.scratch, r, s.stream);
+    });
     if (e != hipSuccess) return e;
-    double l = 1e300, u = -1e300, b = 0.0;
-    for (int k = 0; k < vanse::kReduceBlocks; ++k) {
-        l = std::fmin(l, host[3 * k]);
-        u = std::fmax(u, host[3 * k + 1]);
-        b += host[3 * k + 2];
-    }
-    if (l > u) l = u = 0.0;  // no finite value
-    *lo = l;
-    *hi = u;
-    *bad = b;
+    if (v[0] > v[1]) v[0] = v[1] = 0.0;  // no finite value
+    *lo = v[0];
+    *hi = v[1];
+    *bad = v[2];
     return hipSuccess;
 }
 
@@ -296,11 +343,7 @@ int vanse_set_porosity(vanse_t h, double eps_mean, const double *eps_pert, doubl
         return fail(&s, VANSE_EINVAL, buf);
     }
     if (eps_pert) {
-        if (s.mode == vanse::MODE_F64)
-            e = hipMemcpyAsync(s.pert, eps_pert, sizeof(double) * s.geo.ncells,
-                               hipMemcpyDeviceToDevice, s.stream);
-        else
-            e = vanse::launch_convert_pert(s, eps_pert);
+        e = vanse::launch_take(s.mode, eps_pert, s.pert, s.geo.ncells, 1, 0, s.stream);
     } else {
         e = hipMemsetAsync(s.pert, 0, s.pert_bytes, s.stream);
     }
@@ -354,16 +397,8 @@ int vanse_set_force_field(vanse_t h, const double *F)
             return fail(&s, VANSE_ENOMEM, std::string("vanse_set_force_field: ") + hipGetErrorString(e));
         }
     }
-    for (int d = 0; d < s.d; ++d) {
-        const double *src = F + (size_t)d * s.geo.ncells;
-        char *dst = static_cast<char *>(s.force) + (size_t)d * s.geo.stride * elem;
-        if (s.mode == vanse::MODE_F64)
-            e = hipMemcpyAsync(dst, src, sizeof(double) * s.geo.ncells, hipMemcpyDeviceToDevice,
-                               s.stream);
-        else
-            e = vanse::launch_convert(src, reinterpret_cast<float *>(dst), s.geo.ncells, s.stream);
-        if (e != hipSuccess) return hip_fail(&s, e, "vanse_set_force_field");
-    }
+    e = vanse::launch_take(s.mode, F, s.force, s.geo.ncells, s.d, s.geo.stride, s.stream);
+    if (e != hipSuccess) return hip_fail(&s, e, "vanse_set_force_field");
     s.force_on = true;
     ++s.gen;
     return VANSE_OK;
@@ -377,12 +412,10 @@ int vanse_init(vanse_t h, const double *rho0, const double *u0)
     hipError_t e;
     if (s.mode == vanse::MODE_F16S || s.mode == vanse::MODE_FX16S) {
         // unit of the 16-bit encodings: the mean initial M0, rounded to FP32
-        double *res = s.scratch + 7 * vanse::kReduceBlocks;
         double sum = 0.0;
-        e = vanse::launch_init_mass(s, rho0, res);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&sum, res, sizeof(double), hipMemcpyDeviceToHost, s.stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(s.stream);
+        e = host_result(s.stream, &sum, 1, [&](const vanse::HostResult &r) {
+            return vanse::launch_init_mass(s, rho0, r);
+        });
         if (e != hipSuccess) return hip_fail(&s, e, "vanse_init");
         const double c = (double)(float)(sum / s.geo.ncells);
         if (!std::isfinite(c) || !(c > 0.0))
@@ -454,12 +487,9 @@ int vanse_diagnostics(vanse_t h, double out[7])
     Solver &s = h->s;
     if (!out) return fail(&s, VANSE_EINVAL, "vanse_diagnostics: out is NULL");
     if (!s.initialized) return fail(&s, VANSE_ESTATE, "vanse_diagnostics: call vanse_init first");
-    double *res = s.scratch + 7 * vanse::kReduceBlocks;
-    hipError_t e = vanse::launch_diagnostics(s, (int)(s.t & 1),
-                                             vanse::modulation(s.t, s.period), res);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(out, res, 7 * sizeof(double), hipMemcpyDeviceToHost, s.stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s.stream);
+    hipError_t e = host_result(s.stream, out, 7, [&](const vanse::HostResult &r) {
+        return vanse::launch_diagnostics(s, (int)(s.t & 1), vanse::modulation(s.t, s.period), r);
+    });
     if (e != hipSuccess) return hip_fail(&s, e, "vanse_diagnostics");
     for (int k = 0; k < 7; ++k)
         if (!std::isfinite(out[k])) s.unstable = true;

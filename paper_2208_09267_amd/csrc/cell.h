@@ -184,14 +184,15 @@ struct Cell {
     }
 };
 
-__device__ __forceinline__ Cell locate(const Geometry &g, int c)
+__device__ __forceinline__ Cell locate(const StepArgs &a, int c)
 {
+    const Geometry &g = a.geo;
     Cell k;
     k.c = c;
-    const int x = c % g.nx;
-    const int yz = c / g.nx;
-    const int y = yz % g.ny;
-    const int z = yz / g.ny;
+    const int yz = (int)fdiv((unsigned)c, a.fd_nx);
+    const int x = c - yz * g.nx;
+    const int z = (int)fdiv((unsigned)yz, a.fd_ny);
+    const int y = yz - z * g.ny;
     k.X[0] = (x == 0 ? g.nx : x) - 1;
     k.X[1] = x;
     k.X[2] = (x + 1 == g.nx) ? 0 : x + 1;

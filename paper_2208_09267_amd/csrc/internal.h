@@ -119,8 +119,8 @@ struct Solver {
 
 constexpr int kReduceBlocks = 1024;   // fixed grid of the reduction kernels
 constexpr int kReduceThreads = 256;
-// scratch (doubles): reduction partials [7 * kReduceBlocks], results [7], and
-// from kTrashSlot on a slot that discarded kernel stores may write
+// scratch (doubles): reduction partials [7 * kReduceBlocks], and from
+// kTrashSlot on a slot that discarded kernel stores may write
 constexpr int kTrashSlot = 7 * kReduceBlocks + 32;
 
 double modulation(int64_t n, double period);
@@ -206,10 +206,23 @@ int box_steps(int lattice, int kind);
 // modulation of each.
 hipError_t launch_box(const Solver &s, const StepArgs &a, int kind, const double *m, int k);
 hipError_t launch_init(const Solver &s, const double *rho0, const double *u0);
+// Results of a reduction that the host waits for: pinned host memory that the
+// last kernel writes, and then the flag with the call's ticket.  (A copy to
+// pageable memory and a stream synchronisation cost a call 20 us more.)
+struct HostSlot {
+    double v[8];
+    unsigned long long flag;
+    unsigned long long pad[7];
+};
+struct HostResult {
+    HostSlot *slot = nullptr;      // host address
+    HostSlot *dev = nullptr;       // the same on the device
+    unsigned long long ticket = 0;
+};
 // sum over cells of rho0 phi(x, 0) (the initial M0; rho0 NULL: 1), FP64, in
-// the fixed order of the reductions, into out_dev[0] (device); uses the
-// solver's reduction scratch.
-hipError_t launch_init_mass(const Solver &s, const double *rho0, double *out_dev);
+// the fixed order of the reductions, into out.v[0]; uses the solver's
+// reduction scratch.
+hipError_t launch_init_mass(const Solver &s, const double *rho0, const HostResult &out);
 hipError_t launch_batch_step(int lattice, int mode, bool nt, unsigned nblocks, unsigned block,
                              const BatchMember *members, const unsigned *owner,
                              const double *mtab, const long long *t0, int j, int count,
@@ -236,7 +249,7 @@ hipError_t launch_batch_fused(int mode, unsigned nblocks, size_t lds, const Batc
 hipError_t launch_moments(const Solver &s, int parity, double m, double *rho, double *p,
                           double *u);
 hipError_t launch_populations(const Solver &s, int parity, double *f);
-hipError_t launch_diagnostics(const Solver &s, int parity, double m, double *out_dev);
+hipError_t launch_diagnostics(const Solver &s, int parity, double m, const HostResult &out);
 // Allocation-free diagnostics over caller-owned natural-order FP64 inputs
 // (plane stride g.stride == g.ncells); partials in a fixed per-device array.
 hipError_t launch_diagnostics_noalloc(int lattice, const Geometry &g, const double *f,
@@ -244,11 +257,14 @@ hipError_t launch_diagnostics_noalloc(int lattice, const Geometry &g, const doub
                                       const double F[3], const double *force, double *out,
                                       hipStream_t st);
 size_t noalloc_scratch_bytes();
-hipError_t launch_convert_pert(const Solver &s, const double *src);
-hipError_t launch_convert(const double *src, float *dst, long long n, hipStream_t st);
-// min, max and non-finite count of n FP64 values: per-block triples in
+// `comps` fields of n FP64 values each into the solver's R (double or float)
+// fields `dst`, dst_stride elements apart.
+hipError_t launch_take(int mode, const double *src, void *dst, long long n, int comps,
+                       long long dst_stride, hipStream_t st);
+// min, max and non-finite count of n FP64 values into out.v[0 .. 2], through
 // partials[3 * kReduceBlocks]
-hipError_t launch_range(const double *src, long long n, double *partials, hipStream_t st);
+hipError_t launch_range(const double *src, long long n, double *partials, const HostResult &out,
+                        hipStream_t st);
 hipError_t launch_copy_probe(void *dst, const void *src, int64_t bytes, hipStream_t st);
 
 }  // namespace vanse

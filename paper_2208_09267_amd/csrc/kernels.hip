@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(256) moments_kernel(StepArgs a, int parity,
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= a.geo.ncells) return;
-    const Cell k = locate(a.geo, c);
+    const Cell k = locate(a, c);
     double M0, j[3], rho, p, F[3], u[3];
     macro_f64<L, MODE>(a, k, parity, M0, j, rho, p, F, u);
     if (rho_out) rho_out[c] = rho;
@@ -599,7 +599,7 @@ __global__ void __launch_bounds__(256) populations_kernel(StepArgs a, int parity
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= a.geo.ncells) return;
-    const Cell k = locate(a.geo, c);
+    const Cell k = locate(a, c);
     double fo[L::Q];
     load_natural<L, MODE>(a, k, parity, fo);
     static_for<0, L::Q>([&](auto ic) {
@@ -667,16 +667,26 @@ __global__ void __launch_bounds__(kReduceThreads) diag_kernel(StepArgs a, int pa
                                                               double *__restrict__ partials)
 {
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-    for (int c = blockIdx.x * kReduceThreads + threadIdx.x; c < a.geo.ncells;
-         c += gridDim.x * kReduceThreads) {
-        const Cell k = locate(a.geo, c);
-        double M0, j[3], rho, p, F[3], u[3];
-        macro_f64<L, MODE>(a, k, parity, M0, j, rho, p, F, u);
-        acc[0] += M0;
-        for (int d = 0; d < 3; ++d) {
-            acc[1 + d] += j[d];
-            acc[4 + d] += F[d];
+    // two cells at a time, added in order: the second's loads are in flight
+    // while the first is summed (past the end: the last cell again, not added)
+    const int n = a.geo.ncells, stride = gridDim.x * kReduceThreads;
+    for (int c = blockIdx.x * kReduceThreads + threadIdx.x; c < n; c += 2 * stride) {
+        double M0[2], j[2][3], rho, p, F[2][3], u[3];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const Cell k = locate(a, t == 0 ? c : min(c, n - 1 - stride) + stride);
+            macro_f64<L, MODE>(a, k, parity, M0[t], j[t], rho, p, F[t], u);
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (t == 1 && c >= n - stride) break;
+            acc[0] += M0[t];
+            for (int d = 0; d < 3; ++d) {
+                acc[1 + d] += j[t][d];
+                acc[4 + d] += F[t][d];
+            }
+        }
+        if (c >= n - 2 * stride) break;  // c + 2 stride would pass the end (and 2^31)
     }
     block_reduce<7>(acc, partials + 7 * blockIdx.x);
 }
@@ -697,16 +707,54 @@ __global__ void __launch_bounds__(kReduceThreads) init_mass_kernel(StepArgs a,
     block_reduce<1>(acc, partials + blockIdx.x);
 }
 
+// The results in `out` (pinned host memory) are complete: raise the flag the
+// host polls.  Called by the whole block.
+__device__ __forceinline__ void raise_flag(unsigned long long *flag, unsigned long long ticket)
+{
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(flag, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// flag: NULL when out is device memory that nobody polls
 template <int NV>
 __global__ void __launch_bounds__(kReduceThreads) finalize_kernel(const double *__restrict__ partials,
                                                                   int nblocks,
-                                                                  double *__restrict__ out)
+                                                                  double *__restrict__ out,
+                                                                  unsigned long long *flag,
+                                                                  unsigned long long ticket)
 {
     double acc[NV];
     for (int v = 0; v < NV; ++v) acc[v] = 0.0;
     for (int b = threadIdx.x; b < nblocks; b += kReduceThreads)
         for (int v = 0; v < NV; ++v) acc[v] += partials[NV * b + v];
     block_reduce<NV>(acc, out);
+    if (flag) raise_flag(flag, ticket);
+}
+
+// min and max over a block, and the sum of bad: thread 0 has them.
+__device__ __forceinline__ void block_range(double &lo, double &hi, double &bad)
+{
+    __shared__ double s[3][kReduceThreads / 64];
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fmin(lo, __shfl_down(lo, off, 64));
+        hi = fmax(hi, __shfl_down(hi, off, 64));
+        bad += __shfl_down(bad, off, 64);
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        s[0][wave] = lo;
+        s[1][wave] = hi;
+        s[2][wave] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < kReduceThreads / 64; ++w) {
+            lo = fmin(lo, s[0][w]);
+            hi = fmax(hi, s[1][w]);
+            bad += s[2][w];
+        }
 }
 
 // min, max and non-finite count of n FP64 values (a caller's input array,
@@ -726,31 +774,42 @@ __global__ void __launch_bounds__(kReduceThreads) range_kernel(const double *__r
             hi = fmax(hi, v);
         }
     }
-    __shared__ double s[3][kReduceThreads];
-    s[0][threadIdx.x] = lo;
-    s[1][threadIdx.x] = hi;
-    s[2][threadIdx.x] = bad;
-    __syncthreads();
-    for (int w = kReduceThreads / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            s[0][threadIdx.x] = fmin(s[0][threadIdx.x], s[0][threadIdx.x + w]);
-            s[1][threadIdx.x] = fmax(s[1][threadIdx.x], s[1][threadIdx.x + w]);
-            s[2][threadIdx.x] += s[2][threadIdx.x + w];
-        }
-        __syncthreads();
-    }
+    block_range(lo, hi, bad);
     if (threadIdx.x == 0) {
-        partials[3 * blockIdx.x + 0] = s[0][0];
-        partials[3 * blockIdx.x + 1] = s[1][0];
-        partials[3 * blockIdx.x + 2] = s[2][0];
+        partials[3 * blockIdx.x + 0] = lo;
+        partials[3 * blockIdx.x + 1] = hi;
+        partials[3 * blockIdx.x + 2] = bad;
     }
 }
 
-__global__ void __launch_bounds__(256) convert_pert_kernel(const double *__restrict__ src,
-                                                           float *__restrict__ dst, int n)
+__global__ void __launch_bounds__(kReduceThreads) range_final_kernel(const double *__restrict__ partials,
+                                                                     int nblocks,
+                                                                     double *__restrict__ out,
+                                                                     unsigned long long *flag,
+                                                                     unsigned long long ticket)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < n) dst[c] = float(src[c]);
+    double lo = 1e300, hi = -1e300, bad = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += kReduceThreads) {
+        lo = fmin(lo, partials[3 * b]);
+        hi = fmax(hi, partials[3 * b + 1]);
+        bad += partials[3 * b + 2];
+    }
+    block_range(lo, hi, bad);
+    if (threadIdx.x == 0) {
+        out[0] = lo;
+        out[1] = hi;
+        out[2] = bad;
+    }
+    raise_flag(flag, ticket);
+}
+
+// A caller's fields (blockIdx.y: the component) into the solver's own.
+template <class R>
+__global__ void __launch_bounds__(256) take_kernel(const double *__restrict__ src, R *__restrict__ dst,
+                                                   long long n, long long dst_stride)
+{
+    const long long c = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (c < n) dst[blockIdx.y * dst_stride + c] = R(src[blockIdx.y * n + c]);
 }
 
 // Streaming copy, one 16-byte vector per thread: the best-performing plain
@@ -970,7 +1029,7 @@ hipError_t launch_init(const Solver &s, const double *rho0, const double *u0)
     });
 }
 
-hipError_t launch_init_mass(const Solver &s, const double *rho0, double *out_dev)
+hipError_t launch_init_mass(const Solver &s, const double *rho0, const HostResult &out)
 {
     StepArgs a = step_args(s, 0);
     double *partials = s.scratch;
@@ -980,7 +1039,8 @@ hipError_t launch_init_mass(const Solver &s, const double *rho0, double *out_dev
         init_mass_kernel<float><<<kReduceBlocks, kReduceThreads, 0, s.stream>>>(a, rho0, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    finalize_kernel<1><<<1, kReduceThreads, 0, s.stream>>>(partials, kReduceBlocks, out_dev);
+    finalize_kernel<1><<<1, kReduceThreads, 0, s.stream>>>(partials, kReduceBlocks, out.dev->v,
+                                                           &out.dev->flag, out.ticket);
     return hipGetLastError();
 }
 
@@ -1010,7 +1070,7 @@ hipError_t launch_populations(const Solver &s, int parity, double *f)
     });
 }
 
-hipError_t launch_diagnostics(const Solver &s, int parity, double m, double *out_dev)
+hipError_t launch_diagnostics(const Solver &s, int parity, double m, const HostResult &out)
 {
     StepArgs a = step_args(s, s.t);
     a.m = m;
@@ -1022,7 +1082,8 @@ hipError_t launch_diagnostics(const Solver &s, int parity, double m, double *out
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    finalize_kernel<7><<<1, kReduceThreads, 0, s.stream>>>(partials, kReduceBlocks, out_dev);
+    finalize_kernel<7><<<1, kReduceThreads, 0, s.stream>>>(partials, kReduceBlocks, out.dev->v,
+                                                           &out.dev->flag, out.ticket);
     return hipGetLastError();
 }
 
@@ -1077,6 +1138,8 @@ hipError_t launch_diagnostics_noalloc(int lattice, const Geometry &g, const doub
     if (e != hipSuccess) return e;
     StepArgs a{};
     a.geo = g;
+    a.fd_nx = make_fastdiv((unsigned)g.nx);
+    a.fd_ny = make_fastdiv((unsigned)g.ny);
     a.f = const_cast<double *>(f);
     a.pert = phi;
     a.eps_mean = 0.0;
@@ -1098,29 +1161,30 @@ hipError_t launch_diagnostics_noalloc(int lattice, const Geometry &g, const doub
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    finalize_kernel<7><<<1, kReduceThreads, 0, st>>>(partials, kReduceBlocks, out);
+    finalize_kernel<7><<<1, kReduceThreads, 0, st>>>(partials, kReduceBlocks, out, nullptr, 0);
     return hipGetLastError();
 }
 
-hipError_t launch_convert_pert(const Solver &s, const double *src)
+hipError_t launch_take(int mode, const double *src, void *dst, long long n, int comps,
+                       long long dst_stride, hipStream_t st)
 {
-    convert_pert_kernel<<<blocks_for(s.geo.ncells, 256), 256, 0, s.stream>>>(
-        src, static_cast<float *>(s.pert), s.geo.ncells);
+    const dim3 grid(blocks_for(n, 256), (unsigned)comps);
+    if (mode == MODE_F64)
+        take_kernel<double><<<grid, 256, 0, st>>>(src, static_cast<double *>(dst), n, dst_stride);
+    else
+        take_kernel<float><<<grid, 256, 0, st>>>(src, static_cast<float *>(dst), n, dst_stride);
     return hipGetLastError();
 }
 
-hipError_t launch_convert(const double *src, float *dst, long long n, hipStream_t st)
+hipError_t launch_range(const double *src, long long n, double *partials, const HostResult &out,
+                        hipStream_t st)
 {
-    for (long long off = 0; off < n; off += (1ll << 30)) {
-        const int m = (int)std::min<long long>(n - off, 1ll << 30);
-        convert_pert_kernel<<<blocks_for(m, 256), 256, 0, st>>>(src + off, dst + off, m);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_range(const double *src, long long n, double *partials, hipStream_t st)
-{
-    range_kernel<<<kReduceBlocks, kReduceThreads, 0, st>>>(src, n, partials);
+    // 8 values a thread, so that small fields leave few partials to combine
+    const int nb = (int)std::min<long long>(kReduceBlocks, (n + 8 * kReduceThreads - 1) / (8 * kReduceThreads));
+    range_kernel<<<nb, kReduceThreads, 0, st>>>(src, n, partials);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    range_final_kernel<<<1, kReduceThreads, 0, st>>>(partials, nb, out.dev->v, &out.dev->flag, out.ticket);
     return hipGetLastError();
 }
 
