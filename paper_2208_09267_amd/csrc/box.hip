@@ -96,7 +96,7 @@ __global__ void __launch_bounds__((RX * RY + 63) / 64 * 64) box_kernel(StepArgs 
         for (int n = 0; n < 5; ++n) e[n] = phi_of(em, m, q[n]);
         R I, gx, gy, gz;
         eps_combine<L, R>(e, R(a.wq), R(a.n2), a.qmask, I, gx, gy, gz);
-        collide<L, MODE, R>(v, I, gx, gy, gz, R(a.omega), R(a.fcoef), Fex, Fey, R(a.Fk[2]));
+        collide<L, MODE, R, true>(v, I, gx, gy, gz, R(a.omega), R(a.fcoef), Fex, Fey, R(a.Fk[2]));
     };
     // element of slot i at the cell, and sign * xi_d away
     auto at = [&](auto slotc, auto dirc, auto signc) -> T & {

@@ -291,7 +291,7 @@ __device__ __forceinline__ void march2_tile(const StepArgs &a, unsigned b)
             Fey = add_force<St>(Fey, ld<R, false>(plane + S, fo), a.fscale);
             Fez = add_force<St>(Fez, ld<R, false>(plane + 2 * S, fo), a.fscale);
         }
-        collide<L, MODE, R>(v, I, gx, gy, gz, R(a.omega), R(a.fcoef), Fex, Fey, Fez);
+        collide<L, MODE, R, true>(v, I, gx, gy, gz, R(a.omega), R(a.fcoef), Fex, Fey, Fez);
     };
 
     R up_prev[IPT][Q] = {};  // xi_z = +1 values for plane p - 1 (read at p - 2)
