@@ -1569,9 +1569,13 @@ int vanse_batch_autotune(vanse_batch_t b, int steps_per_trial, int *block, int *
             // whole groups of 4 steps for the two-step launch, an even count
             // for the single-step one (so the members stay at even levels)
             const int t2 = (steps_per_trial + 3) / 4 * 4, t1 = (steps_per_trial + 1) / 2 * 2;
+            // trials of whole chunks replay the captured graph, as the batch's
+            // steps do: launched one by one, single steps of a small batch
+            // cost more than they will (six D3Q27 solves of edges 32-64 in
+            // FP16: two-step launches were picked at 31 GLUPS against 35)
             auto timed = [&](int n, float *per_step) {
                 (void)hipEventRecord(e0, b->stream);
-                rc = batch_run(b, n, false);
+                rc = batch_run(b, n, true);
                 (void)hipEventRecord(e1, b->stream);
                 (void)hipEventSynchronize(e1);
                 float ms = 0.f;
