@@ -1462,6 +1462,7 @@ int vanse_batch_destroy(vanse_batch_t b)
 int vanse_batch_set_stream(vanse_batch_t b, void *stream)
 {
     if (!b) return bfail(nullptr, VANSE_EINVAL, "vanse_batch_set_stream: NULL batch");
+    if (b->stream == static_cast<hipStream_t>(stream)) return VANSE_OK;
     // order the staging events with the new stream
     (void)hipStreamSynchronize(b->stream);
     b->stream = static_cast<hipStream_t>(stream);

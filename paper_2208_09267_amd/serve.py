@@ -7,8 +7,9 @@ cap on the cells in flight allow, keeps every admitted solve's populations
 resident on the device, and advances ALL admitted solves together with the
 batched launch (one kernel per time step covering every solve; chunks of
 steps replay a captured graph).  A solve that reaches its step count is
-retired at the next chunk boundary: its moments are copied to the host and
-its memory is freed, which lets queued requests in.  While the head of the
+retired at the next chunk boundary: its moments are taken and
+its memory is freed, which lets queued requests in; the copy to the host runs
+beside the next steps of the others.  While the head of the
 queue does not fit (or no request is left to arrive), nothing can join
 before the next retirement, so the batch runs straight to it without
 returning to the host between chunks.  Requests that arrive
@@ -162,24 +163,40 @@ class Server:
         self.tuning = (256, vanse.TUNE_TWO_STEP if two_step else 0)
         self._tuned = {}
         self._host = torch.empty(0, dtype=torch.float64)  # pinned staging of the moments
+        self._copies = torch.cuda.Stream()  # device-to-host copies, beside the stepping
 
-    def _to_host(self, solver) -> Tuple[np.ndarray, ...]:
-        """Copy the solve's moments into the pinned staging buffer (grown
-        when needed, then reused) and wait for the copy.  Returns (rho, p, u)
-        views into that buffer, valid until the next call."""
-        fields = solver.moments()
+    def _to_host(self, fields) -> Tuple[torch.Tensor, ...]:
+        """Copy moments that the device has finished into the pinned staging
+        buffer (grown when needed, then reused) on the copy stream, and wait
+        for the copy.  Returns (rho, p, u) views into that buffer, valid until
+        the next call."""
         total = sum(t.numel() for t in fields)
         if self._host.numel() < total:
             self._host = torch.empty(max(total, self._host.numel() * 3 // 2),
                                      dtype=torch.float64, pin_memory=True)
         views, off = [], 0
-        for t in fields:
-            dst = self._host[off:off + t.numel()].view(t.shape)
-            dst.copy_(t, non_blocking=True)
-            views.append(dst)
-            off += t.numel()
-        torch.cuda.current_stream().synchronize()
-        return tuple(v.numpy() for v in views)
+        with torch.cuda.stream(self._copies):
+            for t in fields:
+                dst = self._host[off:off + t.numel()].view(t.shape)
+                dst.copy_(t, non_blocking=True)
+                views.append(dst)
+                off += t.numel()
+        self._copies.synchronize()
+        return tuple(views)
+
+    def _deliver(self, retired, clock, t0):
+        """Hand over the results in `retired` (emptied): (result, moments)."""
+        tr = clock()
+        while retired:
+            result, fields = retired.pop(0)
+            views = self._to_host(fields)
+            result.finish = clock() - t0   # its moments are in host memory
+            if self.keep_fields:
+                # torch's copy is spread over the host's threads
+                result.rho, result.p, result.u = (v.clone().numpy() for v in views)
+            if self.log:
+                self.log(result)
+        self.time["retire"] += clock() - tr
 
     def _bytes(self, work: W.Workload) -> int:
         return state_bytes(work.lattice, work.dims, self.dtype, self.two_step)
@@ -213,6 +230,7 @@ class Server:
         queued_bytes = collections.deque()  # state bytes and cells of the queued requests
         queued_cells = collections.deque()
         active: List[_Active] = []
+        retired = []  # (result, moments on the device) still to be handed over
         results = {}
         batch = None
         dirty = False
@@ -260,6 +278,7 @@ class Server:
                 dirty = True
             self.time["admit"] += clock() - tadm
             if not active:
+                self._deliver(retired, clock, t0)
                 if i < len(arrivals) and realtime:
                     time.sleep(max(0.0, arrivals[i][1][0] - (clock() - t0)))
                 continue
@@ -300,7 +319,15 @@ class Server:
             step = steps_until_host(min(a.remaining for a in active), self.chunk, bool(queue),
                                     i < len(arrivals))
             if step > 0:
-                batch.step(step)
+                # two chunks are launched without waiting: the results of the
+                # solves that retired before are copied out while they run
+                first = min(step, 2 * self.chunk) if retired else step
+                batch.step(first)
+                if retired:
+                    self.time["step"] += clock() - ts
+                    self._deliver(retired, clock, t0)
+                    ts = clock()
+                    batch.step(step - first)
                 for a in active:
                     a.remaining -= step
                 self.stats["chunks"] += 1
@@ -318,17 +345,13 @@ class Server:
                 # update, but it is not stepped before that
                 dirty = True
                 for a in done:
-                    rho, p, u = self._to_host(a.solver)
-                    a.result.finish = clock() - t0   # its moments are in host memory
-                    if self.keep_fields:
-                        a.result.rho, a.result.p, a.result.u = rho.copy(), p.copy(), u.copy()
+                    retired.append((a.result, a.solver.moments()))
                     results[a.rid] = a.result
                     used -= self._bytes(a.work)
-                    a.solver.close()
-                    if self.log:
-                        self.log(a.result)
+                    a.solver.close()  # waits for its moments
                 active = [a for a in active if a.remaining > 0]
                 self.time["retire"] += clock() - tr
+        self._deliver(retired, clock, t0)
         if batch is not None:
             batch.close()
         return [results[r] for r in sorted(results)]
