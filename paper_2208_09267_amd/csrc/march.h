@@ -129,10 +129,17 @@ __device__ __forceinline__ void buffer_store(T v, __amdgpu_buffer_rsrc_t rsrc, u
 // ones, row by row, then the two outer rows -- are dealt to the NT threads in
 // order: cell h NT + tid for pass h < HPT, so an interior cell of pass k < IPT
 // is computed by the same thread in both steps.  PPT: pert values a thread
-// loads per plane.  The passes share one set of registers for the populations
-// in flight, each loading for the next one: a set per pass, a whole plane
-// ahead, cost 19-38 more registers (FP32 1024 threads: 72 bytes of spill) and
-// was no faster where it fitted (FP64 256^3 29.5 against 31.2 GLUPS).
+// loads per plane.
+//
+// TWO: two sets of registers for the populations in flight, so that no value
+// changes its register: with one, the compiler moves the next loads into place
+// where the passes join (19 moves a pass) and waits for them there.  Two are
+// faster wherever the registers hold them -- FX16 256^3 94.4 -> 96.9 GLUPS, FP16
+// 102.3 -> 105.7, FP64 128^3 27.6 -> 28.6, one-pass tiles (FP32 64^3, two rows
+// of 8 planes) 22.7 -> 23.7 -- but FP32 with two passes in 128 VGPRs spills
+// (128^3 60.3 -> 44.1, 64 batched solves 59.3 -> 55.8), and D3Q27 lost 2-3% in
+// FP32 and FP64.  A set per pass, loading a whole plane ahead, spilled too, or was no
+// faster (FP64 256^3 29.5 against 31.2).
 template <class L, int MODE, int IPT, int HPT, int PPT, int NT>
 __device__ __forceinline__ void march2_tile(const StepArgs &a, unsigned b)
 {
@@ -143,6 +150,7 @@ __device__ __forceinline__ void march2_tile(const StepArgs &a, unsigned b)
     using R = typename St::R;
     constexpr int Q = L::Q;
     constexpr int SP = IPT * NT;            // slab cells per direction
+    constexpr bool TWO = HPT == 1 || sizeof(T) == 2 || (sizeof(T) == 8 && Q == 19);
     extern __shared__ __align__(16) unsigned char march_lds[];
 
     const int nx = a.geo.nx, ny = a.geo.ny, nz = a.geo.nz, nxy = a.geo.nxy;
@@ -362,23 +370,46 @@ __device__ __forceinline__ void march2_tile(const StepArgs &a, unsigned b)
                 v[i] = St::decode(r[i]);
             });
         };
-        // a wave's passes form a prefix: each loads for the wave's next pass,
-        // the last one for pass 0 of the next plane
-        auto pass = [&](auto self, auto hc) -> void {
-            constexpr int h = decltype(hc)::value;
-            R v[Q];
-            decode(v, raw);
-            if constexpr (h + 1 < HPT) {
-                const bool more = wbase + (h + 1) * NT < RC;
-                load_cell(raw, more ? pz : pz1, more ? off[h + 1] : off[0]);
-                if (wbase + h * NT < RC) first(hc, v);
-                if (more) self(self, std::integral_constant<int, h + 1>{});
-            } else {
-                load_cell(raw, pz1, off[0]);
-                if (wbase + h * NT < RC) first(hc, v);
-            }
-        };
-        pass(pass, std::integral_constant<int, 0>{});
+        // a wave's passes form a prefix
+        auto wave_on = [&](int h) { return wbase + h * NT < RC; };
+        if constexpr (TWO) {
+            // Pass h works in place on one of two buffers while the other one
+            // loads the wave's next pass; the first then loads pass 0 of the
+            // next plane as soon as no later pass needs it.
+            T other[Q];
+            auto pass = [&](auto hc) {
+                constexpr int h = decltype(hc)::value;
+                if constexpr (h + 1 < HPT)
+                    if (wave_on(h + 1)) load_cell(h % 2 ? raw : other, pz, off[h + 1]);
+                R v[Q];
+                decode(v, h % 2 ? other : raw);
+                first(hc, v);
+            };
+            if (wave_on(0)) pass(std::integral_constant<int, 0>{});
+            if constexpr (HPT <= 2) load_cell(raw, pz1, off[0]);
+            static_for<1, HPT>([&](auto hc) {
+                if (wave_on(decltype(hc)::value)) pass(hc);
+            });
+            if constexpr (HPT > 2) load_cell(raw, pz1, off[0]);
+        } else {
+            // each pass loads for the wave's next one, the last for pass 0 of
+            // the next plane
+            auto pass = [&](auto self, auto hc) -> void {
+                constexpr int h = decltype(hc)::value;
+                R v[Q];
+                decode(v, raw);
+                if constexpr (h + 1 < HPT) {
+                    const bool more = wave_on(h + 1);
+                    load_cell(raw, more ? pz : pz1, more ? off[h + 1] : off[0]);
+                    if (wave_on(h)) first(hc, v);
+                    if (more) self(self, std::integral_constant<int, h + 1>{});
+                } else {
+                    load_cell(raw, pz1, off[0]);
+                    if (wave_on(h)) first(hc, v);
+                }
+            };
+            pass(pass, std::integral_constant<int, 0>{});
+        }
         __syncthreads();  // slab of plane p and ring plane p + 2 complete
         load_pert(ph, znext(znext(pz1)));
         const int z = zprev(pz);  // plane p - 1
