@@ -32,6 +32,7 @@ struct vanse_batch {
     int lattice = 0, mode = 0, count = 0;
     int block = 256;
     bool nt = false;
+    bool remap = false;                 // single steps: each XCD a contiguous range of blocks
     int chunk = 16;                     // steps per captured graph; 0 = no graph
     unsigned nblocks = 0;
     vanse::BatchMember *d_members = nullptr;
@@ -144,6 +145,16 @@ int fail(Solver *s, int code, const std::string &msg)
 int hip_fail(Solver *s, hipError_t e, const char *where)
 {
     return fail(s, VANSE_EDEVICE, std::string(where) + ": " + hipGetErrorString(e));
+}
+
+// compute units of the current GPU
+int device_cus()
+{
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
+        cus = 256;
+    return cus;
 }
 
 // threads per block the step kernel of the lattice is compiled for
@@ -599,7 +610,7 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
 
 namespace {
 struct SoloChoice {
-    int tile_x, tile_y, flat, fused_rows, fused_planes, box;
+    int tile_x, tile_y, flat, fused_rows, fused_planes, box, flags;
 };
 std::mutex g_solo_tune_mu;
 // (lattice, mode, log2 cells, nx, ny % 8) -> launch shape
@@ -618,7 +629,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
     int cls = 0;
     while ((int64_t(1) << (cls + 1)) <= (int64_t)s.geo.ncells) ++cls;
     const auto key = std::make_tuple(s.lattice, s.mode, cls, s.geo.nx, s.geo.ny % 8);
-    SoloChoice best_c{256, 1, 0, 0, 0, 0};
+    SoloChoice best_c{256, 1, 0, 0, 0, 0, 0};
     int64_t run = 0;
     bool cached = false;
     {
@@ -641,8 +652,20 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         // rows, and the flattened launch with 256, 512, 1024 threads; then the
         // two-step launch with 1, 2, 4, 8 rows and 8, 16, 32, 64 planes (and
         // 128 when the lattice has more than 64 planes)
-        std::vector<SoloChoice> cand = {{256, 1, 0, 0, 0, 0}, {256, 2, 0, 0, 0, 0}, {256, 4, 0, 0, 0, 0},
-                                        {256, 1, 1, 0, 0, 0}, {512, 1, 1, 0, 0, 0}, {1024, 1, 1, 0, 0, 0}};
+        std::vector<SoloChoice> cand = {
+            {256, 1, 0, 0, 0, 0, 0}, {256, 2, 0, 0, 0, 0, 0}, {256, 4, 0, 0, 0, 0, 0},
+            {256, 1, 1, 0, 0, 0, 0}, {512, 1, 1, 0, 0, 0, 0}, {1024, 1, 1, 0, 0, 0, 0}};
+        // lattices of at least a wave per CU that the caches hold (up to 2^21
+        // cells): smaller blocks, each XCD a contiguous range of them (a step
+        // then finds most of what the last one wrote in its own L2), and
+        // nontemporal stores.  us a step without and with: 40^3 FP32 5.0 ->
+        // 4.1, 40^3 FP64 7.2 -> 4.9, 32^3 FP32 4.2 -> 3.7, 96^3 FP32 23.5 ->
+        // 22.2; at 256^3 the ranges are slower
+        if (s.geo.ncells >= (1 << 14) && s.geo.ncells <= (1 << 21))
+            for (int threads : {64, 128, 256, 512})
+                for (int f : {(int)VANSE_TUNE_XCD_REMAP, VANSE_TUNE_XCD_REMAP | VANSE_TUNE_NT_STORES,
+                              (int)VANSE_TUNE_NT_STORES})
+                    cand.push_back({threads, 1, 1, 0, 0, 0, f});
         if (s.d == 3) {
             // and the most rows a 512-thread and the largest block take, where
             // those are others: ragged widths, and FP64 and D3Q27 tiles that
@@ -659,14 +682,14 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
                 for (int p : planes) {
                     if (p > 64 && s.geo.nz <= 64) continue;
                     if (r > 0 && vanse::march_tile(s.lattice, s.mode, s.geo, r, 0, nullptr))
-                        cand.push_back({256, 1, 1, r, p, 0});
+                        cand.push_back({256, 1, 1, r, p, 0, 0});
                 }
         }
         // D2Q9: boxes of several steps, each twice (the faster run counts: a
         // trial of a few launches lasts tens of microseconds)
         if (steps_per_trial >= 2)
             for (int kind = 1; vanse::box_steps(s.lattice, kind) > 0; ++kind)
-                for (int run2 = 0; run2 < 2; ++run2) cand.push_back({256, 1, 1, 0, 0, kind});
+                for (int run2 = 0; run2 < 2; ++run2) cand.push_back({256, 1, 1, 0, 0, kind, 0});
         hipEvent_t e0, e1;
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
             return fail(&s, VANSE_EDEVICE, "vanse_autotune: event creation failed");
@@ -686,6 +709,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             s.tile_x = c.tile_x;
             s.tile_y = c.tile_y;
             s.allow_row = !c.flat;
+            s.flags = keep_flags | c.flags;
             (void)hipEventRecord(e0, s.stream);
             rc = vanse_step(h, steps_per_trial);
             (void)hipEventRecord(e1, s.stream);
@@ -709,20 +733,21 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         best_c.tile_x = single_c.tile_x;
         best_c.tile_y = single_c.tile_y;
         best_c.flat = single_c.flat;
+        best_c.flags = single_c.flags;
         std::lock_guard<std::mutex> lk(g_solo_tune_mu);
         g_solo_tune_cache[key] = best_c;
     }
     s.tile_x = best_c.tile_x;
     s.tile_y = best_c.tile_y;
     s.allow_row = !best_c.flat;
-    s.flags = keep_flags;
+    s.flags = keep_flags | best_c.flags;
     int rc = best_c.fused_rows || best_c.box
                  ? multi_step_on(s, best_c.fused_rows, best_c.fused_planes, best_c.box)
                  : vanse_set_fused(h, 0, 0);
     if (rc != VANSE_OK) return rc;
     if (tile_x) *tile_x = best_c.tile_x;
     if (tile_y) *tile_y = best_c.tile_y;
-    if (flags) *flags = keep_flags | (best_c.flat ? VANSE_TUNE_FLAT : 0);
+    if (flags) *flags = s.flags | (best_c.flat ? VANSE_TUNE_FLAT : 0);
     if (fused_rows) *fused_rows = best_c.fused_rows;
     if (fused_planes) *fused_planes = best_c.fused_planes;
     if (steps_run) *steps_run = run;
@@ -904,15 +929,6 @@ int balanced_planes(int nz, int target)
 {
     const int segs = (nz + target - 1) / target;
     return (nz + segs - 1) / segs;
-}
-
-int device_cus()
-{
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-        cus = 256;
-    return cus;
 }
 
 // Estimated duration (in cell-planes) of a batched two-step launch whose
@@ -1229,6 +1245,14 @@ int batch_layout(vanse_batch *b)
         begin += m.nblocks;
     }
     b->nblocks = begin;
+    // Populations that the 256 MB Infinity Cache holds: with a contiguous range
+    // of blocks per XCD a step finds most of them in the L2 that wrote them.
+    // GLUPS with and without: 40 MB (D3Q27 FP16, six solves) 41.7 and 38.2,
+    // 134 MB (two 96^3 FP32) 40.6 and 37.3, 269 MB 36.4 and 37.2, 538 MB 31.3
+    // and 32.9.
+    size_t bytes = 0;
+    for (auto *h : b->members) bytes += h->s.f_bytes;
+    b->remap = bytes <= (size_t)192 << 20;
     hipError_t e = batch_tables(b);
     if (e != hipSuccess)
         return bfail(b, VANSE_ENOMEM, std::string("vanse_batch: tables: ") + hipGetErrorString(e));
@@ -1286,7 +1310,8 @@ hipError_t batch_launch(vanse_batch *b, int j, hipStream_t st)
     const long long *t0 =
         reinterpret_cast<const long long *>(b->d_tab + sizeof(double) * (size_t)b->chunk_cap * b->cap_count);
     return vanse::launch_batch_step(b->lattice, b->mode, b->nt, b->nblocks, (unsigned)b->block,
-                                    b->d_members, b->d_owner, mtab, t0, j, b->count, st);
+                                    b->d_members, b->d_owner, mtab, t0, j, b->count,
+                                    b->remap, st);
 }
 
 hipError_t batch_launch2(vanse_batch *b, int j, int swap, hipStream_t st)

@@ -223,9 +223,10 @@ struct HostResult {
 // the fixed order of the reductions, into out.v[0]; uses the solver's
 // reduction scratch.
 hipError_t launch_init_mass(const Solver &s, const double *rho0, const HostResult &out);
+// remap: each XCD takes one contiguous range of the blocks.
 hipError_t launch_batch_step(int lattice, int mode, bool nt, unsigned nblocks, unsigned block,
                              const BatchMember *members, const unsigned *owner,
-                             const double *mtab, const long long *t0, int j, int count,
+                             const double *mtab, const long long *t0, int j, int count, bool remap,
                              hipStream_t st);
 // Rows of a solve's general tile in the batched two-step launch with blocks
 // of `threads` (kFusedThreads or kGenThreads768) threads (0: none).

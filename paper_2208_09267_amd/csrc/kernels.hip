@@ -156,12 +156,13 @@ __global__ void __launch_bounds__(256) batch_step_kernel(const BatchMember *__re
                                                          const unsigned *__restrict__ owner,
                                                          const double *__restrict__ mtab,
                                                          const long long *__restrict__ t0,
-                                                         int j, int count)
+                                                         int j, int count, bool remap)
 {
-    const unsigned s = owner[blockIdx.x];
+    const unsigned b = remap ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
+    const unsigned s = owner[b];
     StepArgs a = members[s].a;
     a.m = mtab[(long long)j * count + s];
-    const unsigned c = (blockIdx.x - members[s].block_begin) * a.block + threadIdx.x;
+    const unsigned c = (b - members[s].block_begin) * a.block + threadIdx.x;
     if (c >= (unsigned)a.geo.ncells) return;
     const unsigned yz = fdiv(c, a.fd_nx);
     const int x = (int)(c - yz * a.geo.nx);
@@ -1001,7 +1002,7 @@ hipError_t launch_batch_fused(int mode, unsigned nblocks, size_t lds, const Batc
 
 hipError_t launch_batch_step(int lattice, int mode, bool nt, unsigned nblocks, unsigned block,
                              const BatchMember *members, const unsigned *owner,
-                             const double *mtab, const long long *t0, int j, int count,
+                             const double *mtab, const long long *t0, int j, int count, bool remap,
                              hipStream_t st)
 {
     return dispatch(lattice, mode, [&](auto lat, auto m) {
@@ -1009,10 +1010,10 @@ hipError_t launch_batch_step(int lattice, int mode, bool nt, unsigned nblocks, u
         constexpr int M = decltype(m)::value;
         if (nt)
             batch_step_kernel<L, M, true><<<nblocks, block, 0, st>>>(members, owner, mtab, t0, j,
-                                                                    count);
+                                                                    count, remap);
         else
             batch_step_kernel<L, M, false><<<nblocks, block, 0, st>>>(members, owner, mtab, t0,
-                                                                     j, count);
+                                                                     j, count, remap);
         return hipGetLastError();
     });
 }
