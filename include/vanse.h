@@ -167,7 +167,9 @@ int vanse_populations(vanse_t h, double *f);
  *   VANSE_TUNE_FLAT         flattened tiling even when nx is a multiple of block
  *   VANSE_TUNE_NT_STORES    only the population stores carry the nontemporal hint
  * Without VANSE_TUNE_FLAT a block covers `block` consecutive cells of one
- * x-row when nx % block == 0.  Every setting computes bitwise-identical
+ * x-row when nx % block == 0.  Before the first call (or vanse_autotune) a
+ * solve whose populations take at most 192 MB runs with VANSE_TUNE_XCD_REMAP,
+ * a larger one with no flag.  Every setting computes bitwise-identical
  * results; only speed differs.  Errors: EINVAL. */
 enum {
     VANSE_TUNE_NONTEMPORAL = 1,

@@ -72,6 +72,22 @@ double modulation(int64_t n, double period)
     return std::cos(2.0 * M_PI * (double)n / period);
 }
 
+// Solver::flags until the caller or the autotuner chooses.
+constexpr int kFlagsUnset = 1 << 30;
+
+// Flags of a single step.  Not chosen: each XCD a contiguous range of blocks
+// where the 256 MB Infinity Cache holds the populations, so that a step finds
+// part of what the last one wrote in the L2 that wrote it.  us a step without
+// and with: D3Q19 40^3 FP64 (10 MB) 7.3 -> 5.5, 96^3 FP32 (67 MB) 25.0 -> 22.7,
+// 100 x 70 x 93 FP64 (99 MB) 36.1 -> 32.2, 128^3 FP32 (159 MB) 52.7 -> 49.0,
+// D3Q27 64^3 FP64 (57 MB) 18.9 -> 19.1, D2Q9 512^2 FP32 7.2 -> 5.4; 256^3 is
+// slower with it.
+int step_flags(const Solver &s)
+{
+    if (!(s.flags & kFlagsUnset)) return s.flags;
+    return s.f_bytes <= (size_t)192 << 20 ? VANSE_TUNE_XCD_REMAP : 0;
+}
+
 StepArgs step_args(const Solver &s, int64_t n)
 {
     StepArgs a;
@@ -97,7 +113,7 @@ StepArgs step_args(const Solver &s, int64_t n)
     a.wq = n_axes ? quad_weight(n_axes) : 0.0;
     a.n2 = 2.0 * n_axes;
     a.qmask = s.qmask & 7;
-    a.flags = s.flags;
+    a.flags = step_flags(s);
     a.block = (unsigned)(s.tile_x * s.tile_y);
     a.row = (s.allow_row && s.geo.nx % s.tile_x == 0 && s.geo.ny % s.tile_y == 0) ? 1 : 0;
     a.tx = (unsigned)s.tile_x;
@@ -276,6 +292,7 @@ int vanse_create(int lattice, const int64_t dims[3], double tau, int dtype, vans
     s.geo.stride = (ncells + 127) / 128 * 128;
     s.tau = tau;
     s.qmask = s.d == 2 ? 3 : 7;
+    s.flags = vanse::kFlagsUnset;
 
     s.f_bytes = (size_t)s.q * (size_t)s.geo.stride * elem_bytes(dtype);
     s.pert_bytes = (size_t)s.geo.stride * (dtype == VANSE_FP64 ? 8 : 4);
@@ -646,7 +663,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             cached = true;
         }
     }
-    const int keep_flags = s.flags & ~VANSE_TUNE_FLAT;
+    const int keep_flags = s.flags & ~(VANSE_TUNE_FLAT | vanse::kFlagsUnset);
     if (!cached) {
         // single-step candidates: tiled x-row segments of 256 cells with 1, 2, 4
         // rows, and the flattened launch with 256, 512, 1024 threads; then the

@@ -55,6 +55,21 @@ def test_autotuned_solve_equals_single_steps_bitwise(case):
     b.close()
 
 
+@pytest.mark.parametrize("lat,dims,dtype", [
+    ("D3Q19", (1, 1, 1), vanse.FP64), ("D3Q19", (31, 7, 5), vanse.FP32_SHIFTED),
+    ("D3Q27", (64, 9, 11), vanse.FP64), ("D2Q9", (256, 33, 1), vanse.FP16_SHIFTED),
+    ("D3Q19", (110, 110, 109), vanse.FP64), ("D3Q19", (110, 110, 110), vanse.FP64)])  # 192 MB
+def test_untuned_launch_equals_plain_blocks_bitwise(lat, dims, dtype):
+    print("case", lat, dims, dtype, flush=True)
+    a, b = (_solver(lat, dims, dtype, 4) for _ in range(2))
+    b.set_tuning(256, 0)
+    a.step(7)
+    b.step(7)
+    assert _same(_bits(a), _bits(b))
+    a.close()
+    b.close()
+
+
 # members, two-step or not
 BATCHES = [("D3Q19", [(64, 96, 256), (70, 90, 250), (64, 96, 256)], vanse.FP32_SHIFTED, True),
            ("D3Q27", [(48, 120, 320), (50, 131, 310), (33, 97, 330)], vanse.FP64, True),
