@@ -8,8 +8,12 @@ resident on the device, and advances ALL admitted solves together with the
 batched launch (one kernel per time step covering every solve; chunks of
 steps replay a captured graph).  A solve that reaches its step count is
 retired at the next chunk boundary: its moments are taken and
-its memory is freed, which lets queued requests in; the copy to the host runs
-beside the next steps of the others.  While the head of the
+its memory is freed, which lets queued requests in.  The copy to the host runs
+beside the next steps of the others when nothing else has to be done first;
+before a request is admitted, a launch is autotuned or another solve's moments
+are taken, it is waited for, so that a result never waits for the set-up of
+other requests and the moments of one solve at a time are on the device, none
+while new states are allocated.  While the head of the
 queue does not fit (or no request is left to arrive), nothing can join
 before the next retirement, so the batch runs straight to it without
 returning to the host between chunks.  Requests that arrive
@@ -25,6 +29,7 @@ arrays.
 from __future__ import annotations
 
 import collections
+import contextlib
 import dataclasses
 import time
 from typing import List, Optional, Sequence, Tuple
@@ -223,14 +228,22 @@ class Server:
         """Serve `arrivals` (time in seconds from start, workload), in
         arrival order.  realtime=False admits every request at time 0 (an
         offline batch).  Returns one Result per request, in arrival order."""
-        arrivals = sorted(enumerate(arrivals), key=lambda r: r[1][0])
+        retired = []  # the last (result, moments on the device) not yet handed over
         clock = time.perf_counter
         t0 = clock()
+        try:
+            return self._run(arrivals, realtime, retired, clock, t0)
+        except BaseException:
+            with contextlib.suppress(Exception):  # what had finished is not lost
+                self._deliver(retired, clock, t0)
+            raise
+
+    def _run(self, arrivals, realtime, retired, clock, t0) -> List[Result]:
+        arrivals = sorted(enumerate(arrivals), key=lambda r: r[1][0])
         queue = collections.deque()  # (rid, arrival, workload)
         queued_bytes = collections.deque()  # state bytes and cells of the queued requests
         queued_cells = collections.deque()
         active: List[_Active] = []
-        retired = []  # (result, moments on the device) still to be handed over
         results = {}
         batch = None
         dirty = False
@@ -259,6 +272,10 @@ class Server:
                 res.finish = clock() - t0
                 results[rid] = res
                 continue
+            if k:
+                self.time["admit"] += clock() - tadm
+                self._deliver(retired, clock, t0)
+                tadm = clock()
             for _ in range(k):
                 rid, ta, work = queue.popleft()
                 queued_bytes.popleft()
@@ -305,6 +322,9 @@ class Server:
                     # well under a millisecond.
                     trial = tune_trial_steps(min(a.remaining for a in active))
                     if retune(prev[2] if prev else 0, trial):
+                        self.time["rebuild"] += clock() - tr
+                        self._deliver(retired, clock, t0)
+                        tr = clock()
                         block, flags, ran = batch.autotune(trial)
                         self._tuned[cls] = (block, flags, trial)
                         for a in active:
@@ -320,7 +340,7 @@ class Server:
                                     i < len(arrivals))
             if step > 0:
                 # two chunks are launched without waiting: the results of the
-                # solves that retired before are copied out while they run
+                # solve that retired before are copied out while they run
                 first = min(step, 2 * self.chunk) if retired else step
                 batch.step(first)
                 if retired:
@@ -340,17 +360,18 @@ class Server:
             self.time["step"] += clock() - ts
             done = [a for a in active if a.remaining <= 0]
             if done:
-                tr = clock()
                 # the batch keeps the retired members' pointers until the next
                 # update, but it is not stepped before that
                 dirty = True
                 for a in done:
+                    self._deliver(retired, clock, t0)
+                    tr = clock()
                     retired.append((a.result, a.solver.moments()))
                     results[a.rid] = a.result
                     used -= self._bytes(a.work)
                     a.solver.close()  # waits for its moments
+                    self.time["retire"] += clock() - tr
                 active = [a for a in active if a.remaining > 0]
-                self.time["retire"] += clock() - tr
         self._deliver(retired, clock, t0)
         if batch is not None:
             batch.close()
