@@ -343,16 +343,21 @@ int vanse_set_fused(vanse_t h, int rows, int planes);
  * most rows that a 512-thread and the largest block take, which also gives
  * FP64 solves of any width and D3Q27 in FP64 a two-step launch; on D2Q9
  * launches of up to 8 steps on boxes of cells in LDS, twice each) runs
- * `steps_per_trial` REAL steps timed with HIP events, and the fastest is kept and cached for solves of the same
- * lattice, dtype and size class.  *fused_rows / *fused_planes report the
+ * `steps_per_trial` REAL steps timed with HIP events -- launches of several
+ * steps start at an even level (after one step more, where the solve sits at
+ * an odd one) and run steps_per_trial rounded up to whole launches -- and the
+ * fastest per step is kept and cached for solves of the same lattice, dtype
+ * and size class.  A cached choice answers calls with at most the
+ * steps_per_trial that made it; a call with longer trials runs them again and
+ * replaces it.  *fused_rows / *fused_planes report the
  * chosen two-step tile, which need not be one that vanse_set_fused takes
  * (0 / 0: single steps, or D2Q9's boxes; the tile of the single-step kernel
  * is still reported and used for leftover steps).  The two-step and box
  * candidates need the second population array of vanse_set_fused: it is
  * allocated for the trials and freed again unless one of them wins
  * (vanse_set_fused with rows = 0 frees it then).
- * The solve advances (number of candidates) * steps_per_trial steps, or 0
- * when the choice came from the cache (*steps_run tells).  Synchronises.
+ * The solve advances the steps of every trial, or 0 when the choice came from
+ * the cache (*steps_run tells).  Synchronises.
  * Any output pointer may be NULL.  Errors: EINVAL, ESTATE, ENOMEM, EDEVICE. */
 int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int *flags,
                    int *fused_rows, int *fused_planes, int64_t *steps_run);

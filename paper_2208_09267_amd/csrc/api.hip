@@ -550,7 +550,7 @@ int vanse_set_tuning(vanse_t h, int block, int flags)
         return fail(&s, VANSE_EINVAL, "vanse_set_tuning: unknown flag");
     s.tile_x = block;
     s.tile_y = 1;
-    s.flags = flags & (VANSE_TUNE_NONTEMPORAL | VANSE_TUNE_XCD_REMAP | VANSE_TUNE_NT_STORES);
+    s.flags = s.user_flags = flags & (VANSE_TUNE_NONTEMPORAL | VANSE_TUNE_XCD_REMAP | VANSE_TUNE_NT_STORES);
     s.allow_row = (flags & VANSE_TUNE_FLAT) == 0;
     return VANSE_OK;
 }
@@ -628,6 +628,7 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
 namespace {
 struct SoloChoice {
     int tile_x, tile_y, flat, fused_rows, fused_planes, box, flags;
+    int trial = 0;  // the steps per trial that chose it
 };
 std::mutex g_solo_tune_mu;
 // (lattice, mode, log2 cells, nx, ny % 8) -> launch shape
@@ -652,10 +653,11 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
     {
         std::lock_guard<std::mutex> lk(g_solo_tune_mu);
         auto it = g_solo_tune_cache.find(key);
-        // the class key does not fix ny: a two-step tile chosen on another
+        // a choice made on shorter trials than these is tried again; and the
+        // class key does not fix ny: a two-step tile chosen on another
         // lattice of the class may have more rows than this one (or no
-        // compiled shape here), and is then tuned again
-        if (it != g_solo_tune_cache.end() &&
+        // compiled shape here), and is then tuned again too
+        if (it != g_solo_tune_cache.end() && it->second.trial >= steps_per_trial &&
             (it->second.fused_rows == 0 ||
              (it->second.fused_rows <= s.geo.ny &&
               vanse::march_tile(s.lattice, s.mode, s.geo, it->second.fused_rows, 0, nullptr)))) {
@@ -663,7 +665,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             cached = true;
         }
     }
-    const int keep_flags = s.flags & ~(VANSE_TUNE_FLAT | vanse::kFlagsUnset);
+    // the caller's flags apply to every candidate; those of an earlier choice do not
+    const int keep_flags = s.user_flags;
     if (!cached) {
         // single-step candidates: tiled x-row segments of 256 cells with 1, 2, 4
         // rows, and the flattened launch with 256, 512, 1024 threads; then the
@@ -704,9 +707,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         }
         // D2Q9: boxes of several steps, each twice (the faster run counts: a
         // trial of a few launches lasts tens of microseconds)
-        if (steps_per_trial >= 2)
-            for (int kind = 1; vanse::box_steps(s.lattice, kind) > 0; ++kind)
-                for (int run2 = 0; run2 < 2; ++run2) cand.push_back({256, 1, 1, 0, 0, kind, 0});
+        for (int kind = 1; vanse::box_steps(s.lattice, kind) > 0; ++kind)
+            for (int run2 = 0; run2 < 2; ++run2) cand.push_back({256, 1, 1, 0, 0, kind, 0});
         hipEvent_t e0, e1;
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
             return fail(&s, VANSE_EDEVICE, "vanse_autotune: event creation failed");
@@ -727,13 +729,23 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             s.tile_y = c.tile_y;
             s.allow_row = !c.flat;
             s.flags = keep_flags | c.flags;
+            // launches of several steps: whole ones, from an even level (a box
+            // stepped part of the way carries the rim of all its steps, and a
+            // trial from an odd level would time single steps at both ends)
+            const int per_launch = c.box ? vanse::box_steps(s.lattice, c.box) : (c.fused_rows ? 2 : 1);
+            const int trial = (steps_per_trial + per_launch - 1) / per_launch * per_launch;
+            if (per_launch > 1 && (s.t & 1)) {
+                if ((rc = vanse_step(h, 1)) != VANSE_OK) break;
+                ++run;
+            }
             (void)hipEventRecord(e0, s.stream);
-            rc = vanse_step(h, steps_per_trial);
+            rc = vanse_step(h, trial);
             (void)hipEventRecord(e1, s.stream);
             (void)hipEventSynchronize(e1);
             float ms = 0.f;
             (void)hipEventElapsedTime(&ms, e0, e1);
-            run += steps_per_trial;
+            ms /= (float)trial;
+            run += trial;
             if (rc == VANSE_OK && ms < best) {
                 best = ms;
                 best_c = c;
@@ -751,6 +763,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         best_c.tile_y = single_c.tile_y;
         best_c.flat = single_c.flat;
         best_c.flags = single_c.flags;
+        best_c.trial = steps_per_trial;
         std::lock_guard<std::mutex> lk(g_solo_tune_mu);
         g_solo_tune_cache[key] = best_c;
     }

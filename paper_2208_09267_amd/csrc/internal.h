@@ -99,6 +99,7 @@ struct Solver {
     int tile_x = 256;            // step kernel tile: x-row segment per block
     int tile_y = 1;              //   and rows per block
     int flags = 0;               // step-kernel variant flags (StepArgs::flags)
+    int user_flags = 0;          // those of vanse_set_tuning (the autotuner adds its own to them)
     bool allow_row = true;       // use the tiled launch when the tile divides the lattice
     void *f = nullptr;           // populations (current time level)
     size_t f_bytes = 0;

@@ -1,0 +1,64 @@
+"""GPU tests of vanse_autotune's trials and of what it keeps: which calls run
+trials again, how many real steps a trial takes, and what a caller can do with
+the launch it reports."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2208_09267_amd import vanse
+from paper_2208_09267_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _solver(lat, dims, dtype, seed=3, period=31.0):
+    s = vanse.Solver(lat, dims, 0.55 + 0.01 * seed, dtype)
+    d = 2 if lat == "D2Q9" else 3
+    s.set_porosity(0.75, torch.from_numpy(W.fourier_eps(dims, seed=seed)).cuda(), period)
+    s.set_force((1e-6, -2e-7, 3e-7)[:d])
+    s.init(None, torch.from_numpy(np.ascontiguousarray(W.taylor_green(dims, 0.03)[:d])).cuda())
+    return s
+
+
+def _bits(s):
+    return s.populations().cpu().numpy()
+
+
+# size classes that no other test tunes
+@pytest.mark.parametrize("lat,dims,dtype", [("D2Q9", (211, 95, 1), vanse.FX16_SHIFTED),
+                                            ("D3Q19", (53, 31, 23), vanse.FX16_SHIFTED)])
+def test_longer_trials_run_again_and_replace_the_choice(lat, dims, dtype):
+    print("case", lat, dims, dtype, flush=True)
+    a = _solver(lat, dims, dtype)
+    first = a.autotune(2)
+    assert first.steps_run > 0
+    assert a.autotune(1) == first._replace(steps_run=0)
+    longer = a.autotune(8)
+    assert longer.steps_run > first.steps_run
+    assert a.autotune(8) == longer._replace(steps_run=0)
+    assert a.autotune(3) == longer._replace(steps_run=0)
+    a.close()
+
+
+@pytest.mark.parametrize("trial,pre", [(1, 0), (3, 1), (8, 1), (8, 0)])
+def test_d2q9_box_trials_are_whole_launches_from_an_even_level(trial, pre):
+    dims = (64 + trial, 150 + pre, 1)  # a class of its own per case (nx is part of it)
+    print("case", dims, trial, pre, flush=True)
+    a, b = (_solver("D2Q9", dims, vanse.FX16_SHIFTED) for _ in range(2))
+    a.step(pre)
+    run = a.autotune(trial).steps_run
+    # three boxes of 8 steps and two of 4, twice each, trials rounded up
+    boxes = 2 * (3 * (-(-trial // 8) * 8) + 2 * (-(-trial // 4) * 4))
+    singles = run - boxes
+    assert singles > 0
+    # n candidates of one step each, and a step to an even level where they end odd
+    n, extra = divmod(singles, trial)
+    if trial > 1:
+        assert extra == (pre + n * trial) % 2
+    assert (pre + run) % 2 == 0
+    assert a.time == pre + run
+    a.step(29)
+    b.step(a.time)
+    assert np.array_equal(_bits(a), _bits(b), equal_nan=True)
+    a.close()
+    b.close()
