@@ -335,9 +335,11 @@ int vanse_set_fused(vanse_t h, int rows, int planes);
 
 /* Autotune the launch shape of vanse_step: each candidate (tiled 256-cell
  * row segments with 1, 2 or 4 rows per block where they divide the
- * lattice; flat launches of 256, 512 and 1024 threads, and for 2^14 to 2^21
- * cells of 64 to 512 threads with VANSE_TUNE_XCD_REMAP, VANSE_TUNE_NT_STORES
- * or both, which *flags then reports; on 3-D lattices the
+ * lattice; flat launches of 256, 512 and 1024 threads; all these with the
+ * flags of an untuned solve (vanse_set_tuning), and for 2^14 to 2^21 cells, or
+ * populations of at most 192 MB, also without, and flat launches of 64 to 512
+ * threads with and without VANSE_TUNE_XCD_REMAP and VANSE_TUNE_NT_STORES;
+ * *flags reports them; on 3-D lattices the
  * two-step launch of vanse_set_fused with 1, 2, 4 or 8 rows and 8, 16, 32
  * or 64 planes, and 128 when nz > 64, where its shape exists, and with the
  * most rows that a 512-thread and the largest block take, which also gives

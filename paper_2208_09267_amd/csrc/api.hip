@@ -82,11 +82,9 @@ constexpr int kFlagsUnset = 1 << 30;
 // 100 x 70 x 93 FP64 (99 MB) 36.1 -> 32.2, 128^3 FP32 (159 MB) 52.7 -> 49.0,
 // D3Q27 64^3 FP64 (57 MB) 18.9 -> 19.1, D2Q9 512^2 FP32 7.2 -> 5.4; 256^3 is
 // slower with it.
-int step_flags(const Solver &s)
-{
-    if (!(s.flags & kFlagsUnset)) return s.flags;
-    return s.f_bytes <= (size_t)192 << 20 ? VANSE_TUNE_XCD_REMAP : 0;
-}
+constexpr size_t kRemapBytes = (size_t)192 << 20;
+int default_flags(const Solver &s) { return s.f_bytes <= kRemapBytes ? VANSE_TUNE_XCD_REMAP : 0; }
+int step_flags(const Solver &s) { return (s.flags & kFlagsUnset) ? default_flags(s) : s.flags; }
 
 StepArgs step_args(const Solver &s, int64_t n)
 {
@@ -672,20 +670,32 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         // rows, and the flattened launch with 256, 512, 1024 threads; then the
         // two-step launch with 1, 2, 4, 8 rows and 8, 16, 32, 64 planes (and
         // 128 when the lattice has more than 64 planes)
+        // in the order the untuned launch takes them (default_flags), which is
+        // thus one of them
+        const int def = vanse::default_flags(s);
         std::vector<SoloChoice> cand = {
-            {256, 1, 0, 0, 0, 0, 0}, {256, 2, 0, 0, 0, 0, 0}, {256, 4, 0, 0, 0, 0, 0},
-            {256, 1, 1, 0, 0, 0, 0}, {512, 1, 1, 0, 0, 0, 0}, {1024, 1, 1, 0, 0, 0, 0}};
+            {256, 1, 0, 0, 0, 0, def}, {256, 2, 0, 0, 0, 0, def}, {256, 4, 0, 0, 0, 0, def},
+            {256, 1, 1, 0, 0, 0, def}, {512, 1, 1, 0, 0, 0, def}, {1024, 1, 1, 0, 0, 0, def}};
         // lattices of at least a wave per CU that the caches hold (up to 2^21
-        // cells): smaller blocks, each XCD a contiguous range of them (a step
-        // then finds most of what the last one wrote in its own L2), and
-        // nontemporal stores.  us a step without and with: 40^3 FP32 5.0 ->
-        // 4.1, 40^3 FP64 7.2 -> 4.9, 32^3 FP32 4.2 -> 3.7, 96^3 FP32 23.5 ->
-        // 22.2; at 256^3 the ranges are slower
-        if (s.geo.ncells >= (1 << 14) && s.geo.ncells <= (1 << 21))
+        // cells, or as many as default_flags remaps): smaller blocks, each XCD
+        // a contiguous range of them (a step then finds most of what the last
+        // one wrote in its own L2) or not, and nontemporal stores.  us a step
+        // without and with: 40^3 FP32 5.0 -> 4.1, 40^3 FP64 7.2 -> 4.9, 32^3
+        // FP32 4.2 -> 3.7, 96^3 FP32 23.5 -> 22.2; at 256^3 the ranges are slower
+        if (s.geo.ncells >= (1 << 14) && (s.geo.ncells <= (1 << 21) || def)) {
+            auto add = [&](const SoloChoice &c) {
+                for (const SoloChoice &o : cand)
+                    if (o.tile_x == c.tile_x && o.tile_y == c.tile_y && o.flat == c.flat && o.flags == c.flags)
+                        return;
+                cand.push_back(c);
+            };
+            for (int ty : {1, 2, 4}) add({256, ty, 0, 0, 0, 0, 0});
+            add({1024, 1, 1, 0, 0, 0, 0});
             for (int threads : {64, 128, 256, 512})
-                for (int f : {(int)VANSE_TUNE_XCD_REMAP, VANSE_TUNE_XCD_REMAP | VANSE_TUNE_NT_STORES,
+                for (int f : {0, (int)VANSE_TUNE_XCD_REMAP, VANSE_TUNE_XCD_REMAP | VANSE_TUNE_NT_STORES,
                               (int)VANSE_TUNE_NT_STORES})
-                    cand.push_back({threads, 1, 1, 0, 0, 0, f});
+                    add({threads, 1, 1, 0, 0, 0, f});
+        }
         if (s.d == 3) {
             // and the most rows a 512-thread and the largest block take, where
             // those are others: ragged widths, and FP64 and D3Q27 tiles that

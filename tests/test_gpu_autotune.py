@@ -62,3 +62,33 @@ def test_d2q9_box_trials_are_whole_launches_from_an_even_level(trial, pre):
     assert np.array_equal(_bits(a), _bits(b), equal_nan=True)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("lat,dims,dtype", [("D3Q19", (11, 9, 7), vanse.FP64), ("D2Q9", (61, 43, 1), vanse.FP64),
+                                            ("D3Q27", (256, 6, 2), vanse.FP32_SHIFTED)])
+def test_small_lattices_are_tried_in_the_untuned_order(lat, dims, dtype):
+    """Their untuned launch gives each XCD a contiguous range of blocks, and so
+    do the single-step launches they are tuned with."""
+    print("case", lat, dims, dtype, flush=True)
+    a, b = (_solver(lat, dims, dtype) for _ in range(2))
+    assert a.autotune(4).flags & vanse.TUNE_XCD_REMAP
+    a.step(7)
+    b.step(a.time)
+    assert np.array_equal(_bits(a), _bits(b))
+    a.close()
+    b.close()
+
+
+def test_large_lattices_in_16_bits_try_the_untuned_launch():
+    """2.3 M cells of 38 bytes (87 MB) run with ranges of blocks per XCD untuned:
+    the tuner tries them as it does below 2^21 cells, 15 launches more than the
+    those it has for every size (1024 threads and 64 to 512 with each choice of
+    ranges and nontemporal stores; nx is no multiple of the tiled launches' 256)."""
+    s = _solver("D3Q19", (160, 120, 121), vanse.FX16_SHIFTED)
+    run = s.autotune(2).steps_run
+    s.close()
+    # flat: 256, 512, 1024 threads; two-step: as many tiles as at any size
+    t = _solver("D3Q19", (160, 120, 321), vanse.FX16_SHIFTED)  # 234 MB: not remapped
+    base = t.autotune(2).steps_run
+    t.close()
+    assert run - base == 2 * 15
