@@ -357,10 +357,12 @@ int vanse_set_fused(vanse_t h, int rows, int planes);
  * is still reported and used for leftover steps).  The two-step and box
  * candidates need the second population array of vanse_set_fused: it is
  * allocated for the trials and freed again unless one of them wins
- * (vanse_set_fused with rows = 0 frees it then).
+ * (vanse_set_fused with rows = 0 frees it then).  Where it cannot be
+ * allocated the solve gets single steps, and a choice made without these
+ * candidates is not cached.
  * The solve advances the steps of every trial, or 0 when the choice came from
  * the cache (*steps_run tells).  Synchronises.
- * Any output pointer may be NULL.  Errors: EINVAL, ESTATE, ENOMEM, EDEVICE. */
+ * Any output pointer may be NULL.  Errors: EINVAL, ESTATE, EDEVICE. */
 int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int *flags,
                    int *fused_rows, int *fused_planes, int64_t *steps_run);
 

@@ -724,6 +724,7 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             return fail(&s, VANSE_EDEVICE, "vanse_autotune: event creation failed");
         float best = 1e30f, best_single = 1e30f;
         SoloChoice single_c = best_c;
+        bool all_tried = true;
         int rc = VANSE_OK;
         for (const SoloChoice &c : cand) {
             if (rc != VANSE_OK) break;
@@ -731,7 +732,10 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
             if (!c.flat && !tiled_ok) continue;  // would fall back to a flat launch
             if (c.tile_x * c.tile_y > max_threads(s)) continue;
             if (c.fused_rows || c.box) {
-                if (multi_step_on(s, c.fused_rows, c.fused_planes, c.box) != VANSE_OK) continue;
+                if (multi_step_on(s, c.fused_rows, c.fused_planes, c.box) != VANSE_OK) {
+                    all_tried = false;  // no memory for the second array
+                    continue;
+                }
             } else {
                 s.fused_rows = s.fused_planes = s.box = 0;  // keep the second array for later trials
             }
@@ -774,17 +778,24 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         best_c.flat = single_c.flat;
         best_c.flags = single_c.flags;
         best_c.trial = steps_per_trial;
-        std::lock_guard<std::mutex> lk(g_solo_tune_mu);
-        g_solo_tune_cache[key] = best_c;
+        if (all_tried) {
+            std::lock_guard<std::mutex> lk(g_solo_tune_mu);
+            g_solo_tune_cache[key] = best_c;
+        }
     }
     s.tile_x = best_c.tile_x;
     s.tile_y = best_c.tile_y;
     s.allow_row = !best_c.flat;
     s.flags = keep_flags | best_c.flags;
-    int rc = best_c.fused_rows || best_c.box
-                 ? multi_step_on(s, best_c.fused_rows, best_c.fused_planes, best_c.box)
-                 : vanse_set_fused(h, 0, 0);
-    if (rc != VANSE_OK) return rc;
+    if (best_c.fused_rows || best_c.box) {
+        if (multi_step_on(s, best_c.fused_rows, best_c.fused_planes, best_c.box) != VANSE_OK)
+            // a choice of the class that this solve has no memory for: single steps
+            best_c.fused_rows = best_c.fused_planes = best_c.box = 0;
+    }
+    if (!best_c.fused_rows && !best_c.box) {
+        const int rc = vanse_set_fused(h, 0, 0);
+        if (rc != VANSE_OK) return rc;
+    }
     if (tile_x) *tile_x = best_c.tile_x;
     if (tile_y) *tile_y = best_c.tile_y;
     if (flags) *flags = s.flags | (best_c.flat ? VANSE_TUNE_FLAT : 0);

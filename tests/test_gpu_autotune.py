@@ -92,3 +92,46 @@ def test_large_lattices_in_16_bits_try_the_untuned_launch():
     base = t.autotune(2).steps_run
     t.close()
     assert run - base == 2 * 15
+
+
+def _big_plane():
+    """D2Q9 FP64, 67 M cells: 4.8 GB of populations; boxes win by about 2."""
+    dims, dev = (8192, 8192, 1), torch.device("cuda")
+    s = vanse.Solver("D2Q9", dims, 0.7, vanse.FP64)
+    s.set_porosity(0.75, W.fourier_eps_device(dims, 2, dev), 40.0)
+    s.init(None, W.taylor_green_device(dims, 0.02, dev, 2))
+    return s
+
+
+def test_a_choice_without_memory_for_its_second_array_takes_single_steps():
+    a = _big_plane()
+    one = a.device_bytes
+    a.autotune(8)
+    boxes = a.device_bytes > one
+    print("boxes chosen:", boxes, flush=True)
+    a.close()
+    b, c = _big_plane(), _big_plane()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    hog = torch.empty(free - (3 << 30), dtype=torch.uint8, device="cuda")  # 3 GB left
+    assert b.autotune(8).steps_run == 0      # the class has its choice
+    assert b.device_bytes == one
+    short = b.autotune(16)                   # longer trials: without the boxes
+    assert short.steps_run > 0 and b.device_bytes == one
+    assert short.fused_rows == 0
+    b.step(5)
+    assert b.time == short.steps_run + 5
+    del hog
+    torch.cuda.empty_cache()
+    again = c.autotune(16)                   # what was found without memory is not kept
+    assert again.steps_run > short.steps_run
+    assert (c.device_bytes > one) == boxes
+    c.init(None, W.taylor_green_device((8192, 8192, 1), 0.02, torch.device("cuda"), 2))
+    b.init(None, W.taylor_green_device((8192, 8192, 1), 0.02, torch.device("cuda"), 2))
+    for s in (b, c):
+        s.step(11)
+    for x, y in zip(b.moments(), c.moments()):
+        assert torch.equal(x, y)
+    b.close()
+    c.close()
