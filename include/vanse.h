@@ -325,9 +325,12 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y);
  *   D3Q27, FP32/FP16 storage: I = 1 and H <= 2
  *   D3Q27, FP64: none;
  * and the block's LDS (Q * nx * rows stored populations plus 5 * (rows + 4)
- * * nx perturbation values) within 160 KiB.  Blocks have 512 threads, or 1024
- * for D3Q19 tiles in FP32/FP16 storage of more than 512 cells, or more than
- * 1024 with the two outer rows.
+ * * nx perturbation values) within 160 KiB.  With 8, 16, 32, 64 or 128 planes
+ * every tile that vanse_autotune may report is taken too: on any 3-D lattice,
+ * in any storage and for any nx, as many rows as fit the threads of one block
+ * (nx * rows <= 512; D3Q19 in FP32/FP16 storage 1024).  Blocks have 512
+ * threads, or 1024 for D3Q19 tiles in FP32/FP16 storage of more than 512
+ * cells, or more than 1024 with the two outer rows.
  * rows = 0 switches the launch off and frees the second array.
  * Synchronises the solver's stream when it allocates or frees.
  * Errors: EINVAL, ENOMEM. */
@@ -352,9 +355,9 @@ int vanse_set_fused(vanse_t h, int rows, int planes);
  * and size class.  A cached choice answers calls with at most the
  * steps_per_trial that made it; a call with longer trials runs them again and
  * replaces it.  *fused_rows / *fused_planes report the
- * chosen two-step tile, which need not be one that vanse_set_fused takes
- * (0 / 0: single steps, or D2Q9's boxes; the tile of the single-step kernel
- * is still reported and used for leftover steps).  The two-step and box
+ * chosen two-step tile, which vanse_set_fused takes on a solve of the same
+ * lattice, dtype and dims (0 / 0: single steps, or D2Q9's boxes; the tile of
+ * the single-step kernel is still reported and used for leftover steps).  The two-step and box
  * candidates need the second population array of vanse_set_fused: it is
  * allocated for the trials and freed again unless one of them wins
  * (vanse_set_fused with rows = 0 frees it then).  Where it cannot be

@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <initializer_list>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <new>
@@ -589,6 +590,18 @@ int multi_step_on(Solver &s, int rows, int planes, int box)
     s.box = box;
     return VANSE_OK;
 }
+
+// z-planes per segment of the two-step tiles that the autotuner tries.
+constexpr int kTunedPlanes[5] = {8, 16, 32, 64, 128};
+
+// Whether the autotuner may choose a two-step tile that is none of
+// fused_shape's: its rows fit one pass of a block.
+bool tuned_tile(const Solver &s, int rows, int planes)
+{
+    vanse::MarchTile t;
+    return std::find(std::begin(kTunedPlanes), std::end(kTunedPlanes), planes) != std::end(kTunedPlanes) &&
+           vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, &t) && t.ipt == 1;
+}
 }  // namespace
 
 extern "C" {
@@ -613,8 +626,9 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be >= 0 and planes >= 1");
     if (rows > s.geo.ny)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be <= ny");
-    if (!vanse::fused_shape(s.lattice, s.mode, s.geo, rows) ||
-        !vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, nullptr))
+    if (!tuned_tile(s, rows, planes) &&
+        (!vanse::fused_shape(s.lattice, s.mode, s.geo, rows) ||
+         !vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, nullptr)))
         return fail(&s, VANSE_EINVAL,
                     "vanse_set_fused: no compiled tile of nx = " + std::to_string(s.geo.nx) +
                         " x " + std::to_string(rows) + " rows for this lattice and dtype");
@@ -698,8 +712,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
         }
         if (s.d == 3) {
             // and the most rows a 512-thread and the largest block take, where
-            // those are others: ragged widths, and FP64 and D3Q27 tiles that
-            // vanse_set_fused has no shape for
+            // those are others (tuned_tile): ragged widths, and FP64 and D3Q27
+            // tiles beyond those of fused_shape
             std::vector<int> rows = {1, 2, 4, 8};
             for (int &r : rows)
                 if (!vanse::fused_shape(s.lattice, s.mode, s.geo, r)) r = 0;
@@ -707,9 +721,8 @@ int vanse_autotune(vanse_t h, int steps_per_trial, int *tile_x, int *tile_y, int
                 const int r = vanse::march_rows(s.lattice, s.mode, s.geo, nt);
                 if (std::find(rows.begin(), rows.end(), r) == rows.end()) rows.push_back(r);
             }
-            const int planes[5] = {8, 16, 32, 64, 128};
             for (int r : rows)
-                for (int p : planes) {
+                for (int p : kTunedPlanes) {
                     if (p > 64 && s.geo.nz <= 64) continue;
                     if (r > 0 && vanse::march_tile(s.lattice, s.mode, s.geo, r, 0, nullptr))
                         cand.push_back({256, 1, 1, r, p, 0, 0});

@@ -135,3 +135,46 @@ def test_a_choice_without_memory_for_its_second_array_takes_single_steps():
         assert torch.equal(x, y)
     b.close()
     c.close()
+
+
+# two-step tiles that are none of the general rules' (FP64, D3Q27, ragged widths)
+TILES = [("D3Q27", (64, 40, 70), vanse.FP64, 8, 32), ("D3Q27", (64, 40, 10), vanse.FP64, 7, 8),
+         ("D3Q19", (187, 17, 20), vanse.FP64, 2, 16), ("D3Q19", (187, 17, 20), vanse.FP32_SHIFTED, 5, 8),
+         ("D3Q27", (100, 11, 9), vanse.FX16_SHIFTED, 5, 64), ("D3Q27", (256, 6, 5), vanse.FP64, 2, 8),
+         ("D3Q19", (93, 37, 29), vanse.FP16_SHIFTED, 11, 128)]
+
+
+@pytest.mark.parametrize("lat,dims,dtype,rows,planes", TILES)
+def test_a_tile_the_autotuner_may_report_can_be_set(lat, dims, dtype, rows, planes):
+    print("case", lat, dims, dtype, rows, planes, flush=True)
+    a, b = (_solver(lat, dims, dtype) for _ in range(2))
+    a.set_fused(rows, planes)
+    for n in (2, 7, 4):
+        a.step(n)
+        b.step(n)
+    assert np.array_equal(_bits(a), _bits(b), equal_nan=True)
+    with pytest.raises(vanse.VanseError) as e:  # one row more than a block takes
+        a.set_fused(1024 // dims[0] + 1, planes)
+    assert e.value.code == vanse.EINVAL
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("lat,dims,dtype", [("D3Q27", (160, 128, 128), vanse.FP64), ("D3Q19", (187, 141, 93), vanse.FP64),
+                                            ("D3Q19", (250, 61, 64), vanse.FP32_SHIFTED)])
+def test_the_reported_launch_can_be_restored(lat, dims, dtype):
+    print("case", lat, dims, dtype, flush=True)
+    a, b = (_solver(lat, dims, dtype) for _ in range(2))
+    launch = a.autotune(4)
+    print("chosen", launch, flush=True)
+    b.set_tuning(256, launch.flags)
+    b.set_tile(launch.tile_x, launch.tile_y)
+    b.set_fused(launch.fused_rows, launch.fused_planes)
+    assert a.device_bytes == b.device_bytes
+    u0 = torch.from_numpy(np.ascontiguousarray(W.taylor_green(dims, 0.03))).cuda()
+    for s in (a, b):  # the trials ran past the phase in which this flow is stable
+        s.init(None, u0)
+        s.step(11)
+    assert np.array_equal(_bits(a), _bits(b))
+    a.close()
+    b.close()
