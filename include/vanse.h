@@ -331,6 +331,9 @@ int vanse_set_tile(vanse_t h, int tile_x, int tile_y);
  * (nx * rows <= 512; D3Q19 in FP32/FP16 storage 1024).  Blocks have 512
  * threads, or 1024 for D3Q19 tiles in FP32/FP16 storage of more than 512
  * cells, or more than 1024 with the two outer rows.
+ * Where a z-plane of populations or perturbation values takes 2 GiB or more
+ * (nx * (ny + 2) cells of 8 bytes in FP64, 4 in the other modes), the call
+ * leaves the solve on single steps, without a second array.
  * rows = 0 switches the launch off and frees the second array.
  * Synchronises the solver's stream when it allocates or frees.
  * Errors: EINVAL, ENOMEM. */

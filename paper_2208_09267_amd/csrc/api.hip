@@ -626,9 +626,11 @@ int vanse_set_fused(vanse_t h, int rows, int planes)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be >= 0 and planes >= 1");
     if (rows > s.geo.ny)
         return fail(&s, VANSE_EINVAL, "vanse_set_fused: rows must be <= ny");
+    const bool shape = vanse::fused_shape(s.lattice, s.mode, s.geo, rows);
+    // z-planes past the kernel's offsets: single steps, with the same results
+    if (shape && !vanse::march_plane(s.mode, s.geo)) return vanse_set_fused(h, 0, 0);
     if (!tuned_tile(s, rows, planes) &&
-        (!vanse::fused_shape(s.lattice, s.mode, s.geo, rows) ||
-         !vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, nullptr)))
+        (!shape || !vanse::march_tile(s.lattice, s.mode, s.geo, rows, 0, nullptr)))
         return fail(&s, VANSE_EINVAL,
                     "vanse_set_fused: no compiled tile of nx = " + std::to_string(s.geo.nx) +
                         " x " + std::to_string(rows) + " rows for this lattice and dtype");

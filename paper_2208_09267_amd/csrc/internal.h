@@ -175,6 +175,8 @@ size_t fused_lds_bytes(int q, int mode, int nx, int rows);
 struct MarchTile {
     int nt = 0, ipt = 0, hpt = 0, ppt = 0;
 };
+// Whether the kernel's 32-bit offsets reach a z-plane of this size.
+bool march_plane(int mode, const Geometry &g);
 // The compiled tile of `rows` full x-rows in blocks of nt threads (0: the
 // block size chosen for that tile); false if there is none or its LDS does
 // not fit.

@@ -134,11 +134,16 @@ bool march_cover(int lattice, int mode, MarchTile *t)
 
 int march_threads(int lattice, int mode) { return lattice == 1 && mode != MODE_F64 ? 1024 : 512; }
 
+// Byte offsets in a plane of populations or perturbation values, and one row
+// beyond, stay below kMarchNoStore.
+bool march_plane(int mode, const Geometry &g)
+{
+    return ((long long)g.nxy + 2ll * g.nx) * (long long)std::max(t_bytes(mode), r_bytes(mode)) < (1ll << 31);
+}
+
 bool march_tile(int lattice, int mode, const Geometry &g, int rows, int nt, MarchTile *out)
 {
-    if (lattice == 0 || rows < 1 || rows > g.ny) return false;
-    // byte offsets of a plane and its neighbour rows stay below kMarchNoStore
-    if ((long long)g.nxy * 8 + (long long)g.nx * 16 >= (1ll << 31)) return false;
+    if (lattice == 0 || rows < 1 || rows > g.ny || !march_plane(mode, g)) return false;
     if (nt == 0) {
         // two 512-thread blocks per CU where the tile fits them (D3Q19 FP32
         // 128 x 4 at 128^3: 58.7 GLUPS against 50.2 with 1024 threads), else
