@@ -139,8 +139,10 @@ int vanse_set_force_field(vanse_t h, const double *F);
  * EINVAL, EDEVICE. */
 int vanse_init(vanse_t h, const double *rho0, const double *u0);
 
-/* Advance n >= 0 time steps (asynchronous).  Errors: ESTATE, EINVAL,
- * EDEVICE. */
+/* Advance n >= 0 time steps (asynchronous).  May be captured into a graph: an
+ * even n leaves the populations where the call found them, so that a replay
+ * advances the solve by n steps again (with the m(n) of the capture; vanse_time
+ * does not see replays).  Errors: ESTATE, EINVAL, EDEVICE. */
 int vanse_step(vanse_t h, int64_t n);
 
 /* Macroscopic fields at the current time t_n (eqs. density, velocity,

@@ -458,6 +458,40 @@ int vanse_init(vanse_t h, const double *rho0, const double *u0)
     return VANSE_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
+// Steps of the next n that launches of several steps may take.  Each of these
+// launches moves the solve to its other population array; a captured call has
+// to leave it where it was, or a replay would start from the state of the
+// capture again, so an odd one is taken as single steps (which work in place).
+int64_t multi_steps(const Solver &s, int64_t n)
+{
+    if (!s.f_alt || (s.box <= 0 && s.fused_rows <= 0)) return 0;
+    const int64_t odd = s.t & 1;
+    if (n - odd < 2) return 0;
+    const int64_t even = (n - odd) & ~(int64_t)1;
+    if (!capturing(s.stream)) return odd + even;
+    const int64_t per = s.box > 0 ? vanse::box_steps(s.lattice, s.box) : 2;
+    const int64_t launches = (even + per - 1) / per;
+    return launches & 1 ? odd + (launches - 1) * per : odd + even;
+}
+
+}  // namespace
+
+extern "C" {
+
 int vanse_step(vanse_t h, int64_t n)
 {
     if (!h) return fail(nullptr, VANSE_EINVAL, "vanse_step: NULL handle");
@@ -465,12 +499,13 @@ int vanse_step(vanse_t h, int64_t n)
     if (n < 0) return fail(&s, VANSE_EINVAL, "vanse_step: n must be >= 0");
     if (!s.initialized) return fail(&s, VANSE_ESTATE, "vanse_step: call vanse_init first");
     if (s.unstable) return fail(&s, VANSE_EUNSTABLE, "vanse_step: solver is unstable");
+    const int64_t multi = multi_steps(s, n);
     int64_t k = 0;
     while (k < n) {
         const vanse::StepArgs a = vanse::step_args(s, s.t);
-        if (s.box > 0 && s.f_alt && (s.t & 1) == 0 && n - k >= 2) {
+        if (s.box > 0 && (s.t & 1) == 0 && multi - k >= 2) {
             // levels t -> t + c (even) into the second array, which becomes current
-            const int c = (int)std::min<int64_t>(n - k, vanse::box_steps(s.lattice, s.box)) & ~1;
+            const int c = (int)std::min<int64_t>(multi - k, vanse::box_steps(s.lattice, s.box)) & ~1;
             double m[vanse::kBoxMaxSteps];
             for (int j = 0; j < c; ++j) m[j] = vanse::modulation(s.t + j, s.period);
             hipError_t e = vanse::launch_box(s, a, s.box, m, c);
@@ -480,7 +515,7 @@ int vanse_step(vanse_t h, int64_t n)
             k += c;
             continue;
         }
-        if (s.fused_rows > 0 && (s.t & 1) == 0 && n - k >= 2) {
+        if (s.fused_rows > 0 && (s.t & 1) == 0 && multi - k >= 2) {
             // levels t -> t + 2 into the second array, which becomes current
             hipError_t e = vanse::launch_march(s, a);
             if (e != hipSuccess) return hip_fail(&s, e, "vanse_step (two-step launch)");
