@@ -153,7 +153,8 @@ int vanse_moments(vanse_t h, double *rho, double *p, double *u);
 /* Global FP64 sums at t_n, in a fixed (deterministic) order, written to the
  * HOST array out[7]: out[0] = sum_x sum_i f_i (the phi-weighted mass
  * sum rho I), out[1..3] = sum_x sum_i xi_i f_i, out[4..6] = sum_x F.
- * Synchronises.  A non-finite sum (in FX16_SHIFTED also a population at the
+ * Synchronises (as every call that does, it is refused with EDEVICE while its
+ * stream is being captured).  A non-finite sum (in FX16_SHIFTED also a population at the
  * bound of its range) makes h sticky-unstable: this and every later
  * vanse_step return EUNSTABLE. */
 int vanse_diagnostics(vanse_t h, double out[7]);

@@ -180,12 +180,24 @@ size_t elem_bytes(int mode)
     return mode == vanse::MODE_F64 ? 8 : (mode == vanse::MODE_F32S ? 4 : 2);
 }
 
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 // Pinned slots for results the host waits for (HostSlot), shared by all
 // solvers: a call takes one and gives it back before it returns, so there are
 // as many as calls have ever run at once, 32 to a page that is kept until the
-// process ends.
+// process ends.  (Only a call whose stream fails keeps its slot, which a kernel
+// may still write.)
 std::mutex g_slot_mu;
 std::vector<vanse::HostResult> g_slots;
+size_t g_slot_count = 0;                       // slots ever made; g_slots has room for them all
 std::atomic<unsigned long long> g_tickets{0};  // one count for every kind of call
 
 // Run `launch`, which writes its results to the slot it is given and raises its
@@ -193,28 +205,39 @@ std::atomic<unsigned long long> g_tickets{0};  // one count for every kind of ca
 template <class Fn>
 hipError_t host_result(hipStream_t st, double *out, int n, Fn &&launch)
 {
+    // a captured launch would not run, and its answer never come: refused
+    // before anything is recorded
+    if (capturing(st)) return hipErrorStreamCaptureUnsupported;
     vanse::HostResult r;
     {
         std::lock_guard<std::mutex> lk(g_slot_mu);
         if (g_slots.empty()) {
-            constexpr int count = 4096 / sizeof(vanse::HostSlot);
+            constexpr size_t count = 4096 / sizeof(vanse::HostSlot);
+            try {
+                g_slots.reserve(g_slot_count + count);
+            } catch (const std::bad_alloc &) {
+                return hipErrorOutOfMemory;
+            }
             vanse::HostSlot *page = nullptr, *dev = nullptr;
             hipError_t e = hipHostMalloc((void **)&page, 4096,
                                          hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent);
-            if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&dev, page, 0);
+            if (e == hipSuccess && (e = hipHostGetDevicePointer((void **)&dev, page, 0)) != hipSuccess)
+                (void)hipHostFree(page);
             if (e != hipSuccess) return e;
             std::memset(page, 0, 4096);
-            for (int k = 0; k < count; ++k) {
+            for (size_t k = 0; k < count; ++k) {
                 vanse::HostResult q;
                 q.slot = page + k;
                 q.dev = dev + k;
                 g_slots.push_back(q);
             }
+            g_slot_count += count;
         }
         r = g_slots.back();
         g_slots.pop_back();
     }
     r.ticket = ++g_tickets;
+    // the launch that writes the slot is the last one: if it failed, nothing does
     hipError_t e = launch(r);
     if (e == hipSuccess) {
         // poll for up to a millisecond (the answer of an idle stream is here in
@@ -225,13 +248,13 @@ hipError_t host_result(hipStream_t st, double *out, int n, Fn &&launch)
         if (!done()) {
             e = hipStreamSynchronize(st);
             if (e == hipSuccess && !done()) e = hipErrorUnknown;
+            if (e != hipSuccess) return e;
         }
+        std::memcpy(out, r.slot->v, sizeof(double) * (size_t)n);
     }
-    if (e != hipSuccess) return e;  // the slot may still be written: not given back
-    std::memcpy(out, r.slot->v, sizeof(double) * (size_t)n);
     std::lock_guard<std::mutex> lk(g_slot_mu);
     g_slots.push_back(r);
-    return hipSuccess;
+    return e;
 }
 
 // min, max and number of non-finite values of n caller-provided FP64 values
@@ -461,16 +484,6 @@ int vanse_init(vanse_t h, const double *rho0, const double *u0)
 }  // extern "C"
 
 namespace {
-
-bool capturing(hipStream_t st)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status == hipStreamCaptureStatusActive;
-}
 
 // Steps of the next n that launches of several steps may take.  Each of these
 // launches moves the solve to its other population array; a captured call has

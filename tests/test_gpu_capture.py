@@ -56,3 +56,32 @@ def test_captured_steps_replay(lat, dims, dtype, launch, n):
     assert np.array_equal(x, y)
     a.close()
     b.close()
+
+
+def test_calls_that_wait_are_refused_under_capture_and_leave_it_usable():
+    s = _solver("D3Q19", (24, 20, 16), vanse.FP16_SHIFTED)
+    r = _solver("D3Q19", (24, 20, 16), vanse.FP16_SHIFTED)
+    n = 24 * 20 * 16
+    eps, F = torch.zeros(n, dtype=torch.float64, device="cuda"), \
+        torch.zeros((3, n), dtype=torch.float64, device="cuda")
+    s.set_force_field(F)  # its first call allocates
+    s.set_force_field(None)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    refused = 0
+    with torch.cuda.graph(g):
+        s.step(2)
+        for call in (s.diagnostics, lambda: s.set_porosity(0.7, eps), lambda: s.set_force_field(F), s.init):
+            for _ in range(20):
+                with pytest.raises(vanse.VanseError) as e:
+                    call()
+                assert e.value.code == vanse.EDEVICE
+                refused += 1
+        s.step(2)
+    assert refused == 80
+    g.replay()
+    r.step(4)
+    assert np.array_equal(s.populations().cpu().numpy(), r.populations().cpu().numpy())
+    assert s.diagnostics() == r.diagnostics()
+    s.close()
+    r.close()
