@@ -243,7 +243,10 @@ int vanse_batch_set_stream(vanse_batch_t b, void *stream);
  *       at most 62 columns, with a halo column on each side (one wave per
  *       row; vanse_batch_two_step_tiles reports them).  Every member gets a
  *       second population array (allocated here, kept by the member's
- *       solver: its population memory doubles).  Used for every group of 4
+ *       solver: its population memory doubles; where one cannot be
+ *       allocated none is kept, and the call returns ENOMEM, or the batch
+ *       takes single steps where only the tiles of the largest blocks would
+ *       fit its members).  Used for every group of 4
  *       steps of a chunk while all members sit at even time levels (two
  *       launches, so each member ends the group in its first array); other
  *       steps, and batches with a member that has no such tile (smaller

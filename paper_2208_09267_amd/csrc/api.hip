@@ -1187,6 +1187,7 @@ int batch_layout2(vanse_batch *b)
     // 48.8 k, 16 of 40^3 (64 tiles) 42.5 k against 49.1 k.
     std::vector<int> tall(b->count, 0);
     bool use_tall = false;
+    bool only_tall = false;  // no other tile: single steps where tall tiles cannot be had
     if (uni_rows == 0) {
         const int nt = vanse::march_threads(b->lattice, b->mode);
         size_t tiles = 0;
@@ -1201,6 +1202,8 @@ int batch_layout2(vanse_batch *b)
         }
         use_tall = ok && tiles >= (size_t)device_cus();
         if (use_tall) {
+            for (int k = 0; k < b->count && !xt; ++k)
+                only_tall = only_tall || vanse::batch_fused_rows(b->members[k]->s, gen_threads) == 0;
             xt = false;
             gen_threads = nt;
         }
@@ -1273,6 +1276,8 @@ int batch_layout2(vanse_batch *b)
     if (lds > (size_t)vanse::kFusedMaxLds) return VANSE_OK;
     b->layout_f2.assign(b->count, nullptr);
     b->cols2.assign(b->count, 0);
+    std::vector<Solver *> fresh;  // members whose second array is allocated here
+    fresh.reserve(b->count);
     for (int k = 0; k < b->count; ++k) {
         Solver &s = b->members[k]->s;
         if (!s.f_alt) {
@@ -1280,11 +1285,16 @@ int batch_layout2(vanse_batch *b)
             if (e != hipSuccess) {
                 s.f_alt = nullptr;
                 (void)hipGetLastError();
-                // D3Q27 in FP64 has run on single steps alone
-                if (b->lattice == VANSE_D3Q27 && b->mode == vanse::MODE_F64) return VANSE_OK;
+                // no launch will use the others' either
+                for (Solver *f : fresh) {
+                    (void)hipFree(f->f_alt);
+                    f->f_alt = nullptr;
+                }
+                if (only_tall) return VANSE_OK;
                 return bfail(b, VANSE_ENOMEM, std::string("vanse_batch: second population array: ") +
                                                   hipGetErrorString(e));
             }
+            fresh.push_back(&s);
         }
         const int rows = tile_rows(k), cols = tile_cols(k);
         vanse::StepArgs a = vanse::step_args(s, s.t);

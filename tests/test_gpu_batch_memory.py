@@ -1,0 +1,83 @@
+"""GPU tests of a batch whose members' second population arrays do not all fit
+into the memory that is free: nothing stays allocated, and batches that only
+the tiles of the largest blocks fit keep taking single steps."""
+import pytest
+import torch
+
+from paper_2208_09267_amd import vanse
+from paper_2208_09267_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _leave(nbytes):
+    """Take the GPU's free memory but for nbytes."""
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.empty(torch.cuda.mem_get_info()[0] - nbytes, dtype=torch.uint8, device="cuda")
+
+
+def _solver(lat, dims, dtype, seed=2):
+    dev = torch.device("cuda")
+    s = vanse.Solver(lat, dims, 0.7, dtype)
+    s.set_porosity(0.75, W.fourier_eps_device(dims, seed, dev), 40.0)
+    s.init(None, W.taylor_green_device(dims, 0.02, dev, 3))
+    return s
+
+
+# 1.7 and 1.2 GB a member; memory for the second array of one.  FP32 members of
+# this width have other two-step tiles, and the call fails as it did
+@pytest.mark.parametrize("lat,dtype,fails", [("D3Q27", vanse.FP64, False), ("D3Q19", vanse.FP32_SHIFTED, True)])
+def test_a_batch_without_memory_for_all_second_arrays_keeps_none(lat, dtype, fails):
+    dims = (200, 200, 200) if lat == "D3Q27" else (250, 250, 250)
+    print("case", lat, dims, dtype, flush=True)
+    members = [_solver(lat, dims, dtype, k) for k in (1, 2)]
+    alone = [_solver(lat, dims, dtype, k) for k in (1, 2)]
+    one = members[0].device_bytes
+    batch = vanse.Batch(members)
+    hog = _leave(members[0].q * 8 * 200 ** 3 * 3 // 2 if lat == "D3Q27" else 19 * 4 * 250 ** 3 * 3 // 2)
+    if fails:
+        with pytest.raises(vanse.VanseError) as e:
+            batch.set_tuning(256, vanse.TUNE_TWO_STEP, 16)
+        assert e.value.code == vanse.ENOMEM
+    else:
+        batch.set_tuning(256, vanse.TUNE_TWO_STEP, 16)
+    assert [m.device_bytes for m in members] == [one, one]
+    with pytest.raises(vanse.VanseError) as e:
+        batch.two_step_layout()
+    assert e.value.code == vanse.ESTATE
+    batch.set_tuning(256, 0, 16)
+    batch.step(6)
+    del hog
+    torch.cuda.empty_cache()
+    batch.set_tuning(256, vanse.TUNE_TWO_STEP, 16)  # and with the memory
+    assert all(m.device_bytes > one for m in members)
+    batch.step(8)
+    for a, m in zip(alone, members):
+        a.step(14)
+        for x, y in zip(a.moments(), m.moments()):
+            assert torch.equal(x, y)
+    batch.close()
+    for s in members + alone:
+        s.close()
+
+
+def test_a_member_of_more_than_2_29_cells_without_memory_takes_single_steps():
+    dims = (250, 2100, 1025)
+    print("case", dims, flush=True)
+    s = vanse.Solver("D3Q19", dims, 0.7, vanse.FX16_SHIFTED)  # 20 GB
+    s.set_porosity(0.75, None)
+    s.init()
+    one = s.device_bytes
+    batch = vanse.Batch([s])
+    hog = _leave(10 << 30)
+    batch.set_tuning(256, vanse.TUNE_TWO_STEP, 16)
+    assert s.device_bytes == one
+    batch.step(5)
+    assert s.time == 5
+    n = dims[0] * dims[1] * dims[2]
+    assert abs(s.diagnostics()[0] - 0.75 * n) <= 1e-9 * n
+    batch.close()
+    s.close()
+    del hog
+    torch.cuda.empty_cache()
