@@ -1722,10 +1722,16 @@ int vanse_batch_autotune(vanse_batch_t b, int steps_per_trial, int *block, int *
             // trials of whole chunks replay the captured graph, as the batch's
             // steps do: launched one by one, single steps of a small batch
             // cost more than they will (six D3Q27 solves of edges 32-64 in
-            // FP16: two-step launches were picked at 31 GLUPS against 35)
+            // FP16: two-step launches were picked at 31 GLUPS against 35).  Where
+            // the counts differ in their whole chunks (14 and 16 steps), both
+            // are launched one by one.
+            auto replays = [&](int n) {
+                return b->chunk == b->chunk_cap ? n / b->chunk : (n % b->chunk_cap == b->chunk ? 1 : 0);
+            };
+            const bool graph = replays(t1) == replays(t2);
             auto timed = [&](int n, float *per_step) {
                 (void)hipEventRecord(e0, b->stream);
-                rc = batch_run(b, n, true);
+                rc = batch_run(b, n, graph);
                 (void)hipEventRecord(e1, b->stream);
                 (void)hipEventSynchronize(e1);
                 float ms = 0.f;
