@@ -223,7 +223,7 @@ int vanse_batch_set_stream(vanse_batch_t b, void *stream);
  *   VANSE_TUNE_TWO_STEP     advance 3-D batches by the two-step launch (see
  *       vanse_set_fused): when every member has nx = 256 (rows: 4, or 2 in
  *       FP64 or when 4 does not divide ny) or nx = 128 (rows 4, D3Q19) and
- *       those rows divide its ny, all use that compile-time tile
+ *       those rows divide its ny, all use that tile
  *       and their nz is split into equal segments of at most 64 planes (at
  *       most 32, 16 or 8 when a host-side estimate of the launch finds the
  *       batch too small to fill the GPU with 64); otherwise each

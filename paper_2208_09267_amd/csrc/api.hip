@@ -1087,13 +1087,13 @@ double gen_launch_estimate(const std::vector<const vanse::Solver *> &ms,
     return span;
 }
 
-// Segment target of a batched two-step launch: `base` planes (general tiles
-// 32, compile-time tiles 64), or a shorter one of `shorter` when the estimate
-// above predicts the launch at least 8% faster with it (a batch with too few
-// tiles to fill the chip gains more from extra blocks than it loses to the
-// extra planes of shorter segments).  Measured on general tiles (batches of
+// Segment target of a batched two-step launch: `base` planes (uniform batches
+// 64, others 32), or a shorter one of `shorter` when the estimate above
+// predicts the launch at least 8% faster with it (a batch with too few tiles
+// to fill the chip gains more from extra blocks than it loses to the extra
+// planes of shorter segments).  Measured on general tiles (batches of
 // one to 64 solves, 0.5-26 M cells; the estimate's ratios between targets
-// came within 10% of the measured ones) and on compile-time tiles (one to
+// came within 10% of the measured ones) and on uniform batches (one to
 // three 128^3 and one 256^3 solve, FP64/FP32/FP16), the rule picks the
 // fastest target or one within 3% of it.  The estimate counts one block per
 // CU also where two fit: with two, it picked segments too short.
@@ -1116,11 +1116,12 @@ int segment_target(const std::vector<const vanse::Solver *> &ms, const std::vect
 
 // Two-step tables: a tile per member, its second population array
 // (allocated when missing; the member's solver keeps it), and the owner table
-// of that grid.  When every member has the same nx and a compile-time tile of
-// that width divides its ny (batch_uniform_rows), all use that tile and their
+// of that grid.  When every member has the same nx and the rows that
+// batch_uniform_rows gives for it divide its ny, all use that tile and their
 // nz is split into equal segments of at most 64 planes; otherwise each member
-// gets a general tile (batch_fused_rows x-rows) and segments of at most 32
-// planes.  Batches too small to fill the chip take shorter segments
+// gets a tile of its own (as many rows as the largest block takes, or
+// batch_fused_rows of them, or segments of them: below) and segments of at
+// most 32 planes.  Batches too small to fill the chip take shorter segments
 // (segment_target).  Leaves fused_ok false (single steps only) when
 // a member has no tile.
 int batch_layout2(vanse_batch *b)

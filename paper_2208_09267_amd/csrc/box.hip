@@ -29,8 +29,6 @@
 // two steps) lost to single steps at 32^3 to 96^3 (40^3 FP32: 5.8 against 5.5 us).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 #include "cell.h"

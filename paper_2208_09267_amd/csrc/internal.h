@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 
@@ -135,26 +136,16 @@ constexpr int kFusedThreads = 512;    // threads per block the tile rules count 
 // one pass
 constexpr int kGenThreads768 = 768;
 constexpr int kFusedMaxLds = 160 * 1024;
-// Tile shapes vanse_set_fused takes: ipt interior and hpt halo-plane cells per
-// thread of a 512-thread block.  nxc: nx when the tile is one of
-// fused_tile_nx, else 0.
-constexpr bool fused_compiled(int lattice, int mode, int ipt, int hpt, int nxc = 0)
+// Tile shapes vanse_set_fused takes when nx is a multiple of 64 and the rows
+// divide ny: ipt interior and hpt halo-plane cells per thread of a 512-thread
+// block (wide: nx = 256 with 4 rows, which D3Q27 takes too).
+constexpr bool fused_compiled(int lattice, int mode, int ipt, int hpt, bool wide)
 {
     if (lattice == 0 || ipt < 1 || hpt < ipt) return false;
     if (lattice == 2)
-        return mode != MODE_F64 &&
-               (ipt == 1 ? hpt <= 3 : (ipt == 2 && (hpt <= 2 || (nxc == 256 && hpt == 3))));
+        return mode != MODE_F64 && (ipt == 1 ? hpt <= 3 : (ipt == 2 && (hpt <= 2 || (wide && hpt == 3))));
     if (mode == MODE_F64) return ipt == 1 && hpt <= 2;
     return ipt <= 2 && hpt <= ipt + 2;
-}
-// nx if (nx, rows) is one of the benchmarked tiles (D3Q19: 256 x 4, 256 x 2,
-// 128 x 4; D3Q27: 256 x 4, 256 x 2), else 0.
-constexpr int fused_tile_nx(int lattice, int nx, int rows)
-{
-    if (lattice == 1)
-        return ((nx == 256 && (rows == 4 || rows == 2)) || (nx == 128 && rows == 4)) ? nx : 0;
-    if (lattice == 2) return (nx == 256 && (rows == 4 || rows == 2)) ? nx : 0;
-    return 0;
 }
 // The same for any nx and a shorter last tile.
 constexpr bool fused_compiled_gen(int lattice, int mode, int ipt, int hpt)
@@ -164,10 +155,12 @@ constexpr bool fused_compiled_gen(int lattice, int mode, int ipt, int hpt)
     if (mode == MODE_F64) return ipt == 1 && hpt == 1;
     return ipt == 1 ? hpt <= 3 : (ipt == 2 && hpt == 2);
 }
-// Whether vanse_set_fused takes tiles of `rows` full x-rows.
+// Whether vanse_set_fused takes tiles of `rows` full x-rows in segments of any
+// length.
 bool fused_shape(int lattice, int mode, const Geometry &g, int rows);
-// LDS of one 512-thread block by that rule: the population slab and the ring
-// of 5 perturbation planes of rows + 4 x-rows.
+// LDS of one 512-thread block by that rule, and of a full-row member of an
+// x-split batch: the population slab and the ring of 5 perturbation planes of
+// rows + 4 x-rows.
 size_t fused_lds_bytes(int q, int mode, int nx, int rows);
 // Tile of the marching two-step kernel (march.h): threads per block, passes
 // over the interior and over the region with the two outer rows, pert values
@@ -189,6 +182,9 @@ bool march_cover(int lattice, int mode, MarchTile *t);
 int march_rows(int lattice, int mode, const Geometry &g, int nt);
 // Largest block size of the lattice's and storage's tiles.
 int march_threads(int lattice, int mode);
+// Raise a kernel's LDS limit when a block needs more than 64 KiB, once per
+// device.
+hipError_t raise_lds(const void *fn, size_t lds, std::atomic<unsigned long long> &raised);
 size_t march_lds_bytes(int lattice, int mode, int nx, int rows, const MarchTile &t);
 // Two-step launch of one solve: tiles of a.fty x-rows and a.fsz planes.
 hipError_t launch_march(const Solver &s, const StepArgs &a);
@@ -242,9 +238,9 @@ bool batch_xt_tile(const Solver &s, int split_above, int *cols, int *rows);
 // LDS of one block of an x-split tile (cols < nx): slab and a ring of 5
 // perturbation planes of (rows + 4) x (cols + 4) values.
 size_t fused_lds_bytes_xt(int q, int mode, int cols, int rows);
-// Rows of the compile-time tile (nx a compile-time constant) that a batched
-// two-step launch uses when every member has this nx and a multiple of the
-// rows in y (0: none for this lattice, mode and size).
+// Rows of the tile that a batched two-step launch uses when every member has
+// this nx and a multiple of the rows in y (0: none for this lattice, mode and
+// size).
 int batch_uniform_rows(int lattice, int mode, int nx, int ny);
 // x-split tiles of a D3Q19 batch (batch_xt_tile).
 hipError_t launch_batch_fused(int mode, unsigned nblocks, size_t lds, const BatchMember *members,

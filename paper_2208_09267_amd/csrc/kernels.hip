@@ -873,6 +873,19 @@ hipError_t launch_step(const Solver &s, const StepArgs &a, int parity)
     });
 }
 
+hipError_t raise_lds(const void *fn, size_t lds, std::atomic<unsigned long long> &raised)
+{
+    if (lds <= 65536) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (raised.load() & bit) return hipSuccess;
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds);
+    if (e == hipSuccess) raised.fetch_or(bit);
+    return e;
+}
+
 size_t fused_lds_bytes(int q, int mode, int nx, int rows)
 {
     const size_t elem = mode == MODE_F64 ? 8 : (mode == MODE_F32S ? 4 : 2);
@@ -881,10 +894,12 @@ size_t fused_lds_bytes(int q, int mode, int nx, int rows)
     return slab + ring;
 }
 
-// vanse_set_fused takes the shapes whose tile fits the budget below: up to two
-// interior and four halo-plane cells per thread of a 512-thread block, by
-// lattice and storage, and an LDS block of a population slab and a ring of 5
-// perturbation planes.
+// The general rule of vanse_set_fused (every tile it takes is one of
+// march_tile's): up to two interior and four halo-plane cells per thread of a
+// 512-thread block, by lattice and storage, and 160 KiB for a slab of every
+// population and 5 perturbation planes.  That is the budget of x-split tiles
+// (split2_tile), and more than a marching tile needs; it stays the rule, so that
+// calls are accepted and refused alike, whatever kernel runs them.
 bool fused_shape(int lattice, int mode, const Geometry &g, int rows)
 {
     const int nx = g.nx;
@@ -896,7 +911,7 @@ bool fused_shape(int lattice, int mode, const Geometry &g, int rows)
     if (nx % 64 != 0 || g.ny % rows != 0) {
         if ((long long)g.ncells * 8 >= (1ll << 32)) return false;
         if (!fused_compiled_gen(lattice, mode, (int)i, (int)h)) return false;
-    } else if (!fused_compiled(lattice, mode, (int)i, (int)h, fused_tile_nx(lattice, nx, rows))) {
+    } else if (!fused_compiled(lattice, mode, (int)i, (int)h, nx == 256 && rows == 4)) {
         return false;
     }
     const int q = lattice == 0 ? 9 : (lattice == 1 ? 19 : 27);
@@ -982,16 +997,8 @@ hipError_t launch_batch_fused(int mode, unsigned nblocks, size_t lds, const Batc
             constexpr int PER = M == MODE_F64 ? 1 : 2;
             auto *fn = &batch_split2_kernel<L, M, PER, PER>;
             static std::atomic<unsigned long long> raised{0};
-            int dev = 0;
-            hipError_t rc = hipGetDevice(&dev);
+            const hipError_t rc = raise_lds(reinterpret_cast<const void *>(fn), lds, raised);
             if (rc != hipSuccess) return rc;
-            const unsigned long long bit = 1ull << (dev & 63);
-            if (lds > 65536 && !(raised.load() & bit)) {
-                rc = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds);
-                if (rc != hipSuccess) return rc;
-                raised.fetch_or(bit);
-            }
             fn<<<nblocks, kFusedThreads, lds, st>>>(members, owner, mtab, j, count, swap);
             return hipGetLastError();
         } else {

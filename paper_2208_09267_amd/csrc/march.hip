@@ -45,21 +45,6 @@ namespace {
 size_t r_bytes(int mode) { return mode == MODE_F64 ? 8 : 4; }
 size_t t_bytes(int mode) { return mode == MODE_F64 ? 8 : (mode == MODE_F32S ? 4 : 2); }
 
-// Raise a kernel's LDS limit when a block needs more than 64 KiB, once per
-// device.
-hipError_t raise_lds(const void *fn, size_t lds, std::atomic<unsigned long long> &raised)
-{
-    if (lds <= 65536) return hipSuccess;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const unsigned long long bit = 1ull << (dev & 63);
-    if (raised.load() & bit) return hipSuccess;
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFusedMaxLds);
-    if (e == hipSuccess) raised.fetch_or(bit);
-    return e;
-}
-
 // The compiled tiles.  fn(lat, mode, ipt, hpt, ppt, nt, waves) as compile-time
 // constants, for the first that covers t's passes.
 template <class Fn>
@@ -184,13 +169,16 @@ hipError_t launch_march(const Solver &s, const StepArgs &a)
     const unsigned nzb = (unsigned)((a.geo.nz + (int)a.fsz - 1) / (int)a.fsz);
     hipError_t rc = hipErrorInvalidValue;
     march_shapes(s.lattice, s.mode, t, [&](auto lat, auto m, auto i, auto h, auto p, auto n, auto w) {
-        auto *fn = &fused2_kernel<decltype(lat), decltype(m)::value, decltype(i)::value,
-                                  decltype(h)::value, decltype(p)::value, decltype(n)::value,
-                                  decltype(w)::value>;
-        static std::atomic<unsigned long long> raised{0};
-        if ((rc = raise_lds(reinterpret_cast<const void *>(fn), lds, raised)) != hipSuccess) return;
-        fn<<<a.fnyb * nzb, decltype(n)::value, lds, s.stream>>>(a);
-        rc = hipGetLastError();
+        // march_tile's choices (nt = 0): 768 threads are for batches
+        if constexpr (decltype(n)::value != kGenThreads768) {
+            auto *fn = &fused2_kernel<decltype(lat), decltype(m)::value, decltype(i)::value,
+                                      decltype(h)::value, decltype(p)::value, decltype(n)::value,
+                                      decltype(w)::value>;
+            static std::atomic<unsigned long long> raised{0};
+            if ((rc = raise_lds(reinterpret_cast<const void *>(fn), lds, raised)) != hipSuccess) return;
+            fn<<<a.fnyb * nzb, decltype(n)::value, lds, s.stream>>>(a);
+            rc = hipGetLastError();
+        }
     });
     return rc;
 }
