@@ -66,8 +66,9 @@ def measured_traffic(variant, kernel):
     return None if k is None else round(k["bytes_per_launch"])
 
 
-# launch shapes the autotuner picks for this workload on MI355X (used with
-# --fixed-launch, e.g. under a counter profiler that perturbs timing)
+# launch shapes of this workload for --fixed-launch, e.g. under a counter
+# profiler that perturbs timing: the ones the autotuner picks on MI355X, except
+# FP32, where it picks 2 rows x 128 planes (--fixed-shape)
 # (tile_x, tile_y, flat, two-step rows, two-step planes)
 FIXED_LAUNCH = {"fp32_shifted": (1024, 1, True, 4, 64), "fp64": (512, 1, True, 2, 128),
                 "fp16_shifted": (256, 4, False, 4, 64), "fx16_shifted": (256, 4, False, 4, 64)}

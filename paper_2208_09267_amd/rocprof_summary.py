@@ -11,6 +11,7 @@ Usage (repository root):
   python -m paper_2208_09267_amd.rocprof_summary stats DIR
   python -m paper_2208_09267_amd.rocprof_summary trace DIR
   python -m paper_2208_09267_amd.rocprof_summary sq DIR [DIR ...]
+  python -m paper_2208_09267_amd.rocprof_summary counters DIR [DIR ...]
   python -m paper_2208_09267_amd.rocprof_summary traffic FETCH_DIR WRITE_DIR [FETCH_DIR WRITE_DIR ...] OUT_JSON
 """
 from __future__ import annotations
@@ -164,7 +165,11 @@ _BATCH256_CELLS = 4 * 256 ** 3   # four 256^3 solves
 
 def _workload(short, grid):
     """(workload name, cells) of a launch in a bench.py run, from the kernel
-    name and its grid size; (None, None) for other kernels."""
+    name and its grid size; (None, None) for other kernels and for a two-step
+    launch that could be either size's.  (Of the 128^3 and 256^3 solves of a
+    bench.py run only the FP64 ones meet in one lattice and mode.  Their 512-cell
+    tiles differ in the phi values per thread: 4 rows of 128 with 2 on each side
+    are 1024, two a thread; 2 rows of 256 and any other of its tiles more.)"""
     lat = "D2Q9" if "D2Q9" in short else ("D3Q27" if "D3Q27" in short else "D3Q19")
     if short.startswith("batch_fused2"):
         if grid >= 1000000:  # 1024 blocks of 1024 threads; the 64 solves: 762
@@ -177,7 +182,13 @@ def _workload(short, grid):
     if lat == "D2Q9" and short.startswith("step_kernel"):
         return "D2Q9 64^2", 64 * 64
     if short.startswith("fused2"):
-        return ("D3Q19 128^3", 128 ** 3) if ", 2, 512, " in short else (lat + " 256^3", 256 ** 3)
+        m = re.match(r"fused2_kernel<D3Q19, 0, (\d+), (\d+), (\d+), (\d+), \d+>", short)
+        if m is None:
+            return lat + " 256^3", 256 ** 3
+        ipt, _, ppt, threads = (int(v) for v in m.groups())
+        if ppt * threads <= 1024:
+            return "D3Q19 128^3", 128 ** 3
+        return (None, None) if ipt > 1 or threads > 512 else ("D3Q19 256^3", 256 ** 3)
     if short.startswith("step_kernel"):
         return ("D3Q19 128^3", 128 ** 3) if grid < 4000000 else (lat + " 256^3", 256 ** 3)
     return None, None
@@ -247,7 +258,29 @@ def sq(directories):
     return out
 
 
+def counters(directories):
+    """{(kernel, grid size): {counter: mean per dispatch}} of every vanse kernel
+    in the given --pmc runs of one program (one counter group per run)."""
+    per = {}
+    for d in directories:
+        with open(_one(os.path.join(d, "*counter_collection.csv"))) as fh:
+            for row in csv.DictReader(fh):
+                name = row["Kernel_Name"]
+                if "vanse::" not in name:
+                    continue
+                short = re.sub(r"\(.*\)$", "", name).replace("void ", "").replace("vanse::", "")
+                per.setdefault((short, int(row["Grid_Size"])), {}).setdefault(
+                    row["Counter_Name"], []).append(float(row["Counter_Value"]))
+    return {k: {c: sum(v) / len(v) for c, v in cs.items()} for k, cs in per.items()}
+
+
 def main(argv):
+    if len(argv) >= 2 and argv[0] == "counters":
+        for (short, grid), m in sorted(counters(argv[1:]).items()):
+            print("%s grid %d" % (short, grid))
+            for k in sorted(m):
+                print("  %-28s %.5g" % (k, m[k]))
+        return 0
     if len(argv) >= 2 and argv[0] == "sq":
         for label, m in sorted(sq(argv[1:]).items()):
             print(label)
