@@ -21,7 +21,7 @@ struct Geometry {
     long long stride;
 };
 
-// Division by a launch-invariant divisor d (see fdiv in kernels.hip).
+// Division by a launch-invariant divisor d (see fdiv in cell.h).
 struct FastDiv {
     unsigned m;  // < 2^32 for every d >= 1
     unsigned s;
@@ -64,7 +64,7 @@ struct StepArgs {
     unsigned nseg;       // tiled: segments per x-row (nx / tx)
     unsigned nyb;        // tiled: row blocks per z-plane (ny / ty)
     FastDiv fd_nx, fd_ny, fd_seg, fd_nyb;
-    // two-step launch (fused2_kernel): n -> n + 2 from f into f2
+    // two-step launch (march.h): n -> n + 2 from f into f2
     void *f2;            // destination populations (natural order at n + 2)
     double m2;           // modulation m(n + 1) of the second step
     unsigned fty;        // full x-rows per tile

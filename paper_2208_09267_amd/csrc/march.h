@@ -22,9 +22,12 @@
 // collide) and the intermediate values pass through the storage encoding as
 // they would through HBM, so one launch is bitwise equal to two single steps.
 //
-// What bounds it: wide tiles move their populations through 2 Q strided streams
-// (D3Q19 256^3: FP32 5.2 TB/s, FP64 5.0); narrow ones and the 16-bit modes are
-// bound by their vector instructions.  So everything that does not change from
+// What bounds it (counters of the launches the autotuner picks, D3Q19 256^3):
+// FP32, 2 rows x 128 planes, moves 2.78 GB a launch (1.06 times what it needs)
+// at 5.4 TB/s, the rate of 2 Q strided streams, with its vector ALUs busy 66% of
+// the time; FP64, 2 x 128, reads its outer rows twice (6.86 GB, 1.31 times) at
+// 6.5 TB/s and waits for loads at 2 waves per SIMD, ALUs 36%; the 16-bit modes,
+// 4 x 64, are bound by their vector instructions.  So everything that does not change from
 // plane to plane is kept per lane -- a cell's byte offset in its plane, its
 // place in the slab (and from it in the phi ring), its destination rows -- and a
 // plane costs scalar additions per direction and a few vector ones: 277 vector
@@ -134,7 +137,8 @@ __device__ __forceinline__ void buffer_store(T v, __amdgpu_buffer_rsrc_t rsrc, u
 // TWO: two sets of registers for the populations in flight, so that no value
 // changes its register: with one, the compiler moves the next loads into place
 // where the passes join (19 moves a pass) and waits for them there.  Two are
-// faster wherever the registers hold them -- FX16 256^3 94.4 -> 96.9 GLUPS, FP16
+// faster where the registers hold them (D3Q19 FP16 with four phi values a
+// thread is 2 VGPRs short and spills 12 bytes a lane) -- FX16 256^3 94.4 -> 96.9 GLUPS, FP16
 // 102.3 -> 105.7, FP64 128^3 27.6 -> 28.6, one-pass tiles (FP32 64^3, two rows
 // of 8 planes) 22.7 -> 23.7 -- but FP32 with two passes in 128 VGPRs spills
 // (128^3 60.3 -> 44.1, 64 batched solves 59.3 -> 55.8), and D3Q27 lost 2-3% in
