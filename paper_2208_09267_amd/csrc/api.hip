@@ -28,6 +28,7 @@ struct vanse_solver {
 
 struct vanse_batch {
     std::vector<vanse_t> members;
+    bool laid_out = false;              // the tables below are complete
     std::vector<void *> layout_f;       // members' population arrays in the member table
     std::vector<unsigned long long> layout_gen;  // members' parameter generations in the tables
     int lattice = 0, mode = 0, count = 0;
@@ -987,6 +988,8 @@ std::map<std::tuple<int, int, int>, TuneChoice> g_tune_cache;
 
 int bfail(vanse_batch *b, int code, const std::string &msg)
 {
+    // the next launch's check must not find the failed allocation
+    if (code == VANSE_ENOMEM) (void)hipGetLastError();
     if (b)
         b->err = msg;
     else
@@ -1349,6 +1352,7 @@ int batch_layout2(vanse_batch *b)
 // (Re)build the member and owner tables for the current block size.
 int batch_layout(vanse_batch *b)
 {
+    b->laid_out = b->fused_ok = false;
     std::vector<vanse::BatchMember> mem(b->count);
     std::vector<unsigned> owner;
     unsigned begin = 0;
@@ -1405,6 +1409,7 @@ int batch_layout(vanse_batch *b)
         (void)hipGraphExecDestroy(b->gexec);
         b->gexec = nullptr;
     }
+    b->laid_out = true;
     return b->two_step ? batch_layout2(b) : VANSE_OK;
 }
 
@@ -1490,7 +1495,7 @@ int batch_capture(vanse_batch *b, bool two)
 
 int batch_run(vanse_batch *b, int64_t n, bool allow_graph)
 {
-    bool moved = false;
+    bool moved = !b->laid_out;  // the last build of the tables failed
     for (int k = 0; k < b->count; ++k) {
         const Solver &s = b->members[k]->s;
         if (s.unstable) return bfail(b, VANSE_EUNSTABLE, "vanse_batch_step: a member is unstable");

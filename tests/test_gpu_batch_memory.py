@@ -81,3 +81,39 @@ def test_a_member_of_more_than_2_29_cells_without_memory_takes_single_steps():
     s.close()
     del hog
     torch.cuda.empty_cache()
+
+
+def test_a_batch_whose_tables_could_not_be_built_is_not_stepped_on_them():
+    small = _solver("D3Q19", (16, 12, 10), vanse.FX16_SHIFTED)
+    big = vanse.Solver("D3Q19", (1280, 1280, 1280), 0.7, vanse.FX16_SHIFTED)  # 80 GB
+    big.set_porosity(0.75, None)
+    big.init()
+    batch = vanse.Batch([small])
+    batch.set_tuning(64, 0, 16)  # 33 M blocks for the big member: 131 MB of owners
+    batch.step(2)
+    hog = [_leave(512 << 20)]  # then 16 MB at a time: the free size reported is not exact
+    try:
+        while len(hog) < 100:
+            hog.append(torch.empty(16 << 20, dtype=torch.uint8, device="cuda"))
+    except torch.cuda.OutOfMemoryError:
+        pass
+    print("blocks of 16 MB past the reported free size less 512 MB:", len(hog) - 1, flush=True)
+    del hog[-4:]
+    torch.cuda.empty_cache()  # 64 MB free, less than the table
+    for call in (lambda: batch.update([big]), lambda: batch.step(1), lambda: batch.step(20)):
+        with pytest.raises(vanse.VanseError) as e:
+            call()
+        assert e.value.code == vanse.ENOMEM
+    assert big.time == 0
+    with pytest.raises(vanse.VanseError) as e:
+        batch.two_step_layout()
+    assert e.value.code == vanse.ESTATE
+    del hog
+    torch.cuda.empty_cache()
+    batch.step(2)  # with the memory: the tables are built
+    assert big.time == 2 and small.time == 2
+    n = 1280 ** 3
+    assert abs(big.diagnostics()[0] - 0.75 * n) <= 1e-9 * n
+    batch.close()
+    for s in (small, big):
+        s.close()
